@@ -152,7 +152,7 @@ hipError_t launch_cls_rows(float* hidden, const int32_t* cls_rows, int n, const 
                            const float* pos0, int d, hipStream_t s);
 
 // Tile sizes the host must know about.
-constexpr int kAttnBQ_f32 = 64;     // query rows per attention workgroup, fp32 path
+constexpr int kAttnBQ_f32 = 16;     // query rows per attention workgroup, fp32 path
 constexpr int kAttnBQ_window = 128; // bf16 path, windowed layers (windows are short segments: one query tile per wave)
 constexpr int kVtAlign = 64;        // segment starts in the transposed-V buffer are multiples of this
 

@@ -425,3 +425,17 @@ def test_stream_reference_reads_and_writes_what_it_says():
     assert not d_out[:10].any() and np.array_equal(d_out[10:].cpu().numpy().view(np.uint32), want[10:])
     with pytest.raises(B.TcmvError):
         B.tcmv_op_stream(d_in, 24, d_out, 16)
+
+
+# (m, n, k): 16x16 tiles (k a multiple of 16, few tiles) at their edges, 64x64 tiles with vector loads and a ragged last
+# slice, and with many tiles
+@pytest.mark.parametrize("m,n,k", [(1, 1, 16), (17, 33, 4096), (16, 16, 80), (65, 64, 148), (1100, 1024, 32), (1025, 1001, 64)])
+@pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESID])
+def test_gemm_f32_tile_edges(m, n, k, epi):
+    test_gemm_f32(m, n, k, epi)
+
+
+@pytest.mark.parametrize("dh", [16, 48, 112, 128])
+def test_attention_f32_head_sizes(dh):
+    """Segments around the 16-query and 16-key tiles and the four waves that share the keys; every remaining head size."""
+    test_attention([15, 16, 17, 1, 63, 64, 65, 80], 2 * dh, 2, 3.0 / dh ** 0.5 * 4, "f32")
