@@ -4,8 +4,8 @@
 // the same way: direct global -> LDS loads (16 bytes per lane, no registers in
 // between) into tiles of 64 k-elements per row (128 bytes), with the 16-byte
 // chunk index XOR-swizzled by (row/2)%8 so that the per-lane 16-byte MFMA operand
-// reads are conflict-free.  LDS is double buffered and the next tile's loads are
-// issued before the current tile's MFMAs.  Each wave owns a (BM/WM) x (BN/WN)
+// reads are conflict-free.  LDS holds two to four such tiles and the loads of
+// the next ones are in flight during the current tile's MFMAs.  Each wave owns a (BM/WM) x (BN/WN)
 // sub-tile built from v_mfma_f32_32x32x16_bf16.
 //
 // The MFMA is issued with W as the row operand and A as the column operand, so
@@ -31,9 +31,13 @@
 // offset), and the last tile of a dimension is shifted back to end at the matrix
 // edge so that no load ever leaves the operand (its repeated rows / columns are
 // skipped when it is written out).
-// Smaller products use one workgroup per tile: 128x128 (4 waves, two per CU),
-// 64x64 (2 waves) for a single small request; a long contraction over few rows
-// that accumulates into the residual stream is cut into four slices of k whose
+// Smaller products use one workgroup per tile, from a set of tile shapes of which the launcher takes the one it
+// estimates to be fastest (kTileKernels).  What bounds them is how long a k-tile takes to arrive (with two stages it is
+// requested one iteration ahead) and the bytes that go from L2 to LDS (128x128 tiles: 11 TB/s at 700 TFLOP/s), so
+// these kernels keep up to four stages in flight and the tiles that fill LDS once per CU may let two waves share a
+// sub-tile, each with half of the k-steps: the wave tiles stay large (64x160: 7 fragment reads for 10 MFMAs) where the
+// workgroup's is small.  4096 x 1280 x 5120: 79 -> 63 us; 256 x 3840 x 1280: 11.8 -> 8.0; 64 x 5120 x 5120: 58 -> 33.
+// A long contraction over few rows that accumulates into the residual stream is cut into four slices of k whose
 // fp32 partial sums a second kernel adds in slice order.
 //
 // Workgroups are numbered so that the eight XCDs (workgroup id mod 8) each walk
@@ -337,14 +341,17 @@ __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[MI][NI], const GemmA
 }
 
 
-template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, int MINB, int EPI>
-__global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_bf16_kernel(GemmArgs g) {
-  constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32;
+// waits until at most N vector-memory loads of this wave are in flight and its LDS reads are back
+template <int N>
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
+
+template <int BM, int BN, int WM, int WN, int KW, int NSTAGE, int MINB, int EPI>
+__global__ __launch_bounds__(WM* WN* KW * 64, MINB) void gemm_bf16_kernel(GemmArgs g) {
+  constexpr int BK = 64, TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32;
   constexpr int ROWB = BK * 2;                     // bytes per staged row
-  constexpr int CPR = BK / 8;                      // 16-byte chunks per row (8 or 4)
-  constexpr int SW_SHIFT = (CPR == 8) ? 1 : 2;     // rows that share a swizzle value (span 256 bytes = all banks)
+  constexpr int CPR = BK / 8;                      // 16-byte chunks per row
+  constexpr int SW_SHIFT = 1;                      // rows that share a swizzle value (span 256 bytes = all banks)
   constexpr int RPL = 64 / CPR;                    // rows covered by one wave-wide load
-  static_assert(BK == 64 || BK == 32, "BK");
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB, STAGE = A_BYTES + B_BYTES;
 
@@ -369,7 +376,7 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_bf16_kernel(GemmArgs g
   const int n0 = tn * BN;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+  const int wm = wave / WN % WM, wn = wave % WN, kw = KW > 1 ? wave / (WM * WN) : 0;
   const uint16_t* A = reinterpret_cast<const uint16_t*>(g.a);
   const uint16_t* W = reinterpret_cast<const uint16_t*>(g.w);
 
@@ -377,7 +384,7 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_bf16_kernel(GemmArgs g
   // 16-byte chunks (RPL rows) of the stage; each lane fetches the global chunk that
   // belongs at its swizzled LDS position.  Rows past the end of the operand are
   // clamped to its last row (they only feed outputs that are never stored).
-  constexpr int WAVES = WM * WN;
+  constexpr int WAVES = WM * WN * KW;
   constexpr int NLA = BM / RPL / WAVES, NLB = BN / RPL / WAVES;      // wave-loads per wave and k-tile
   static_assert(BM % (RPL * WAVES) == 0 && BN % (RPL * WAVES) == 0, "tile/waves mismatch");
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -422,19 +429,21 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_bf16_kernel(GemmArgs g
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
 
-  // Two LDS stages.  The barrier of a k-tile sits before its LAST k-step, not before its first: by then every
+  // NSTAGE LDS stages.  The barrier of a k-tile sits before its LAST k-step, not before its first: by then every
   // wave has read all of the tile's fragments into registers (so the tile's stage can be refilled with tile
-  // kt+2 right after the barrier) and tile kt+1, requested a tile earlier, has had three quarters of an
-  // iteration to land.  After the barrier a wave asks for the first fragments of tile kt+1 and then still has
-  // the MFMAs of the last k-step of tile kt to issue, so no wave sits behind a barrier with nothing to do while
-  // its fragments travel.
-  static_assert(NSTAGE == 2 && BK / 16 >= 2, "the k-loop is written for two stages");
+  // kt+NSTAGE right after the barrier) and tile kt+1 has had at least three quarters of an iteration to land; only
+  // its loads are waited for, those of the NSTAGE-2 tiles behind it stay in flight.  After the barrier a wave asks
+  // for the first fragments of tile kt+1 and then still has the MFMAs of the last k-step of tile kt to issue, so no
+  // wave sits behind a barrier with nothing to do while its fragments travel.
+  static_assert(NSTAGE >= 2 && (NSTAGE - 1) * (NLA + NLB) <= 63, "loads in flight are counted in six bits");
+  constexpr int KK = BK / 16 / KW;      // k-steps of a wave in a k-tile
+  static_assert(KK % 2 == 0, "the register buffers alternate");
   const int lr = lane & 31, lg = lane >> 5;
   bf16x8 af[2][MI], bfr[2][NI];        // fragments double-buffered in registers
   auto frags = [&](int stage, int kk, int b) {
     const uint8_t* sa = smem + stage * STAGE;
     const uint8_t* sb = sa + A_BYTES;
-    const int ch = kk * 2 + lg;
+    const int ch = (kw * KK + kk) * 2 + lg;
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
       const int row = wm * TM + mi * 32 + lr;
@@ -453,16 +462,18 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_bf16_kernel(GemmArgs g
       for (int ni = 0; ni < NI; ++ni)
         acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[b][ni], af[b][mi], acc[mi][ni], 0, 0, 0);
   };
-  constexpr int KK = BK / 16;
-  load_tiles(0, 0);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  constexpr int NL = NLA + NLB;
+#pragma unroll
+  for (int i = 0; i < NSTAGE; ++i)
+    if (i < nk) load_tiles(i, i);
+  if (nk >= NSTAGE) wait_loads<(NSTAGE - 1) * NL>();
+  else wait_loads<0>();
   __syncthreads();                     // tile 0 visible to all waves
-  if (1 < nk) load_tiles(1, 1);
   frags(0, 0, 0);
-  // mode 2: tile kt+2 exists and is requested; 1: tile kt+1 is the last; 0: tile kt is the last
-  auto iteration = [&](int kt, auto mode_c) {
-    constexpr int MODE = decltype(mode_c)::value;
-    const int cur = kt & 1;
+  // REST: k-tiles behind this one, NSTAGE standing for "at least NSTAGE" (tile kt+NSTAGE is then requested)
+  auto iteration = [&](int kt, int cur, auto rest_c) {
+    constexpr int REST = decltype(rest_c)::value;
+    const int next = cur + 1 == NSTAGE ? 0 : cur + 1;
 #pragma unroll
     for (int kk = 0; kk + 1 < KK; ++kk) {
       frags(cur, kk + 1, (kk + 1) & 1);
@@ -479,16 +490,16 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_bf16_kernel(GemmArgs g
         if (NM > NR) __builtin_amdgcn_sched_group_barrier(0x008, NM - NR, 0);
       }
     }
-    if (MODE >= 1) {
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    if (REST >= 1) {
+      wait_loads<(REST >= NSTAGE ? NSTAGE - 2 : REST - 1) * NL>();
       __syncthreads();
-      if (MODE == 2) load_tiles(kt + 2, cur);
-      frags(cur ^ 1, 0, KK & 1);
+      if (REST == NSTAGE) load_tiles(kt + NSTAGE, cur);
+      frags(next, 0, 0);
     }
     mfmas((KK - 1) & 1);
-    if (MODE >= 1) {
+    if (REST >= 1) {
       // after the barrier: an MFMA first, then the tile loads and fragment reads one by one between the MFMAs
-      constexpr int NR = MI + NI, NM = MI * NI, NV = (MODE == 2) ? NLA + NLB : 0;
+      constexpr int NR = MI + NI, NM = MI * NI, NV = (REST == NSTAGE) ? NL : 0;
 #pragma unroll
       for (int i = 0; i < NM; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -498,26 +509,66 @@ __global__ __launch_bounds__(WM* WN * 64, MINB) void gemm_bf16_kernel(GemmArgs g
     }
   };
   {
-    int kt = 0;
-    for (; kt + 2 < nk; ++kt) iteration(kt, std::integral_constant<int, 2>{});
-    if (kt + 1 < nk) { iteration(kt, std::integral_constant<int, 1>{}); ++kt; }
-    iteration(kt, std::integral_constant<int, 0>{});
+    int kt = 0, cur = 0;
+    auto step = [&] { ++kt; cur = cur + 1 == NSTAGE ? 0 : cur + 1; };
+    for (; kt + NSTAGE < nk; step()) iteration(kt, cur, std::integral_constant<int, NSTAGE>{});
+    static_for<NSTAGE>([&](auto i) {
+      constexpr int rest = NSTAGE - 1 - decltype(i)::value;
+      if (nk - 1 - kt >= rest) { iteration(kt, cur, std::integral_constant<int, rest>{}); step(); }
+    });
   }
 
   // ---- epilogue: through the operand stages, which every wave has finished with
   static_assert(WAVES * kEpWaveBytes <= NSTAGE * STAGE, "epilogue staging does not fit in the operand stages");
   __syncthreads();
-  {
-    float* ep = reinterpret_cast<float*>(smem + wave * kEpWaveBytes);
-    const TileBounds tb{0, g.m, 0, g.n, slice};
+  const TileBounds tb{0, g.m, 0, g.n, slice};
+  const int wcol0 = n0 + wn * TN;
+  const bool full = m0 + BM <= g.m && n0 + BN <= g.n;
+  float* ep = reinterpret_cast<float*>(smem + wave * kEpWaveBytes);
+  if constexpr (KW == 1) {
     const int64_t m_base = m0 + wm * TM;
-    const int wcol0 = n0 + wn * TN;
-    if (m0 + BM <= g.m && n0 + BN <= g.n) wave_epilogue<EPI, MI, NI, true>(acc, g, ep, m_base, wcol0, lane, tb);
+    if (full) wave_epilogue<EPI, MI, NI, true>(acc, g, ep, m_base, wcol0, lane, tb);
     else wave_epilogue<EPI, MI, NI, false>(acc, g, ep, m_base, wcol0, lane, tb);
+  } else {
+    // the two waves of a sub-tile hold the sums of different k-steps: each hands one half of its rows to the other
+    static_assert(KW == 2 && MI % 2 == 0 && WAVES * (MI / 2) * NI * 4096 <= NSTAGE * STAGE, "exchange area");
+    constexpr int H = MI / 2;
+    f32x16 mine[H][NI];
+    float4* out = reinterpret_cast<float4*>(smem) + (size_t)wave * H * NI * 256 + lane;
+    const float4* in = reinterpret_cast<const float4*>(smem) + (size_t)(wave ^ (WM * WN)) * H * NI * 256 + lane;
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float t[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int v = 4 * q + j;
+            t[j] = kw ? acc[h][ni][v] : acc[H + h][ni][v];
+            mine[h][ni][v] = kw ? acc[H + h][ni][v] : acc[h][ni][v];
+          }
+          out[((h * NI + ni) * 4 + q) * 64] = make_float4(t[0], t[1], t[2], t[3]);
+        }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 t = in[((h * NI + ni) * 4 + q) * 64];
+          mine[h][ni][4 * q] += t.x; mine[h][ni][4 * q + 1] += t.y; mine[h][ni][4 * q + 2] += t.z; mine[h][ni][4 * q + 3] += t.w;
+        }
+    __syncthreads();
+    const int64_t m_base = m0 + wm * TM + kw * (H * 32);
+    if (full) wave_epilogue<EPI, H, NI, true>(mine, g, ep, m_base, wcol0, lane, tb);
+    else wave_epilogue<EPI, H, NI, false>(mine, g, ep, m_base, wcol0, lane, tb);
   }
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int NSTAGE, int MINB>
+template <int BM, int BN, int WM, int WN, int KW, int NSTAGE, int MINB, bool SPLIT = false>
 static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s) {
   const int tiles_n = (a.n + BN - 1) / BN;
   const int64_t tiles_m = (a.m + BM - 1) / BM;
@@ -525,11 +576,11 @@ static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s) {
   if (total <= 0) return hipSuccess;
   if (total > (1 << 30)) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)(((total + 7) / 8) * 8);
-  const size_t lds = (size_t)NSTAGE * (BM + BN) * BK * 2;
-  dim3 block(WM * WN * 64);
+  const size_t lds = (size_t)NSTAGE * (BM + BN) * 128;
+  dim3 block(WM * WN * KW * 64);
 #define TCMV_GEMM_CASE(E)                                                                              \
   case E: {                                                                                            \
-    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, BK, NSTAGE, MINB, E>;                                 \
+    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, KW, NSTAGE, MINB, E>;                                 \
     if (lds > 64 * 1024) {                                                                             \
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                          \
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);        \
@@ -538,10 +589,17 @@ static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(kern, dim3(grid), block, lds, s, a);                                            \
     break;                                                                                             \
   }
-  switch (a.epi) {
-    TCMV_GEMM_CASE(EPI_STORE) TCMV_GEMM_CASE(EPI_GELU) TCMV_GEMM_CASE(EPI_RESID)
-    TCMV_GEMM_CASE(EPI_EMBED) TCMV_GEMM_CASE(EPI_QKV) TCMV_GEMM_CASE(EPI_GATED) TCMV_GEMM_CASE(EPI_PARTIAL)
-    default: return hipErrorInvalidValue;
+  if constexpr (SPLIT) {
+    switch (a.epi) {
+      TCMV_GEMM_CASE(EPI_PARTIAL)
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    switch (a.epi) {
+      TCMV_GEMM_CASE(EPI_STORE) TCMV_GEMM_CASE(EPI_GELU) TCMV_GEMM_CASE(EPI_RESID)
+      TCMV_GEMM_CASE(EPI_EMBED) TCMV_GEMM_CASE(EPI_QKV) TCMV_GEMM_CASE(EPI_GATED)
+      default: return hipErrorInvalidValue;
+    }
   }
 #undef TCMV_GEMM_CASE
   return hipGetLastError();
@@ -813,7 +871,34 @@ static hipError_t launch_persist(const GemmArgs& a, hipStream_t s) {
 
 
 namespace {
-enum GemmKernel { GK_INVALID, GK_P320, GK_P256, GK_SPLITK, GK_T64, GK_T128 };
+enum GemmKernel { GK_INVALID, GK_P320, GK_P256, GK_T192x256, GK_T256x160, GK_T256x128, GK_T128x160, GK_T128K2, GK_T128, GK_T64, GK_SPLIT128, GK_SPLIT64 };
+
+// Tile kernels and what one workgroup's tile costs: `base` microseconds (launch, first loads, write-out) plus `per_k` for
+// every 64 elements of k.  Those with shared = 0 fill a CU's LDS (rounds of 256 tiles); of the shared ones two (T128)
+// or three (T64) run on a CU, where the cost of a k-tile grows with the tiles per CU from a floor, the memory latency.
+// Fitted to measurements at 256 .. 18432 rows, n 1024 .. 6912, k 1024 .. 5120; of 39 such products the choice is within
+// 3 % of the best kernel on 35, within 10 % on the others.
+struct TileKernel { GemmKernel kernel; int bm, bn, wave_n, shared; float base, per_k, floor_k; };
+constexpr TileKernel kTileKernels[] = {
+    {GK_P256, 256, 256, 64, 0, 5.0f, 1.65f, 0.f},      {GK_P320, 256, 320, 160, 0, 8.0f, 1.75f, 0.f},
+    {GK_T192x256, 192, 256, 128, 0, 8.0f, 1.40f, 0.f}, {GK_T256x160, 256, 160, 160, 0, 9.0f, 1.05f, 0.f},
+    {GK_T256x128, 256, 128, 64, 0, 7.5f, 0.85f, 0.f},  {GK_T128x160, 128, 160, 160, 0, 5.0f, 0.70f, 0.f},
+    {GK_T128K2, 128, 128, 64, 0, 3.5f, 0.53f, 0.f},    {GK_T128, 128, 128, 64, 1, 6.0f, 0.55f, 0.80f},
+    {GK_T64, 64, 64, 32, 1, 2.0f, 0.22f, 0.36f}};
+
+float tile_cost(const TileKernel& t, int64_t m, int n, int k, int slices) {
+  const int64_t tiles = ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn) * slices;
+  const float per_cu = (float)((tiles + 255) / 256), nk = (float)(k / 64 / slices);
+  return t.shared ? t.base + nk * std::max(t.floor_k, t.per_k * per_cu) : per_cu * (t.base + nk * t.per_k);
+}
+
+// a wave tile of `wave_n` columns computes key norms: whole heads, at most four, starting at head boundaries
+bool wave_tile_holds_heads(int wave_n, int qcols, int dh) {
+  return (dh == 64 || dh == 80) && wave_n % dh == 0 && wave_n / dh <= 4 && qcols % wave_n == 0;
+}
+
+bool is_persistent(GemmKernel k) { return k == GK_P320 || k == GK_P256; }
+
 // which kernel a product runs on, and the width of its wave tiles
 GemmKernel choose_kernel(const GemmArgs& a, int* wave_tile_n, int* block_n) {
   if (a.k <= 0 || a.k % 64 || a.lda % 8 || a.n <= 0 || a.n % 8 || a.ldc % 4) return GK_INVALID;
@@ -822,13 +907,14 @@ GemmKernel choose_kernel(const GemmArgs& a, int* wave_tile_n, int* block_n) {
   if (a.epi == EPI_GATED && (a.ldc % 4)) return GK_INVALID;
   // operand element offsets are kept in 32 bits
   if ((double)a.m * (double)a.lda >= 4294967296.0 || (double)a.n * (double)a.k >= 4294967296.0) return GK_INVALID;
+  // The persistent kernels shift their last tile back to the matrix edge and address their operands in bytes, 32 bits.
+  const bool can_persist = a.k >= 128 && a.m >= 256 && a.n >= 320 && a.epi != EPI_PARTIAL &&
+                           (double)a.m * (double)a.lda < 2147483648.0 && (double)a.n * (double)a.k < 2147483648.0;
   // Persistent 256-row tiles (8 waves, one workgroup per CU) from about one and a half rounds of them over the 256
   // CUs.  A tile 320 columns wide is taken where it needs no more tile area x rounds than a 256-wide one (hidden
-  // sizes that are multiples of 320 but not of 256, such as 1280).  That kernel addresses its operands in bytes,
-  // 32 bits.
+  // sizes that are multiples of 320 but not of 256, such as 1280).
   const int64_t big_tiles = ((a.m + 255) / 256) * ((a.n + 255) / 256);
-  if (big_tiles >= 400 && a.k >= 128 && a.m >= 256 && a.n >= 320 && a.epi != EPI_PARTIAL &&
-      (double)a.m * (double)a.lda < 2147483648.0 && (double)a.n * (double)a.k < 2147483648.0) {
+  if (big_tiles >= 400 && can_persist) {
     auto area = [&](int64_t bm, int64_t bn) {
       const int64_t t = ((a.m + bm - 1) / bm) * ((a.n + bn - 1) / bn);
       return ((t + 255) / 256) * bm * bn;
@@ -837,28 +923,46 @@ GemmKernel choose_kernel(const GemmArgs& a, int* wave_tile_n, int* block_n) {
     *wave_tile_n = 64; *block_n = 256;
     return GK_P256;
   }
-  // a single small request: fewer than 200 tiles of 128x128 leave most CUs idle; 64x64 tiles
-  // (2 waves) quadruple the number of workgroups
-  const int64_t mid_tiles = ((a.m + 127) / 128) * ((a.n + 127) / 128);
-  *wave_tile_n = 64; *block_n = 128;
-  // a long contraction over few rows (fc2 of one small request): 64x64 tiles would each walk all of k and
-  // re-read both operands from L2 twice as often; 128x128 tiles over a quarter of k each give as many
-  // workgroups with a quarter of the iterations.  The slices are added to C in a fixed order afterwards.
-  if (mid_tiles < 200 && a.epi == EPI_RESID && a.partial && a.k >= 2048 && (a.k / 64) % 4 == 0) return GK_SPLITK;
-  if (mid_tiles < 200) { *wave_tile_n = 32; *block_n = 64; return GK_T64; }
-  return GK_T128;
+  // Smaller products: a few rounds of tiles at most, so the round that is only partly filled decides.  The kernel with
+  // the lowest estimate is taken (4096 x 1280 x 5120: 63 us with 128x160 tiles, 79 with 128x128; 4096 x 5120 x 1280:
+  // 54 with one round of 256x320 tiles, 79 with 128x128; 256 x 5120 x 1280: 14 with 64x64, 20 - 27 with larger tiles).
+  // Where key norms are wanted (kn_dh), a tile that cannot compute them pays for the separate pass over the keys
+  // (13 us at 4096 rows, 21 at 25772).
+  const TileKernel* best = nullptr;
+  float best_cost = 0.f;
+  for (const TileKernel& t : kTileKernels) {
+    if (is_persistent(t.kernel) && !can_persist) continue;
+    float c = tile_cost(t, a.m, a.n, a.k, 1);
+    if (a.epi == EPI_QKV && a.kn_dh &&
+        !(wave_tile_holds_heads(t.wave_n, a.qcols, a.kn_dh) && (!is_persistent(t.kernel) || a.n % t.bn == 0)))
+      c += 11.5f + 4e-4f * (float)a.m;
+    if (!best || c < best_cost) { best = &t; best_cost = c; }
+  }
+  *wave_tile_n = best->wave_n; *block_n = best->bn;
+  // A long contraction over few rows that accumulates (fc2 of one small request): a quarter of k per workgroup, added
+  // to C in a fixed order by a second kernel, where that is estimated to win in spite of it (256 x 1280 x 5120: 16 us
+  // with 64x64 tiles, 30 unsplit; 1120 rows: 34 with 128x128 tiles, 37 unsplit).
+  if (a.epi == EPI_RESID && a.partial && a.k >= 2048 && (a.k / 64) % 4 == 0) {
+    GemmKernel split = GK_INVALID;
+    for (const TileKernel& t : kTileKernels) {
+      if (!t.shared) continue;
+      const float c = tile_cost(t, a.m, a.n, a.k, 4) + 3.9f + 1.75e-6f * (float)a.m * (float)a.n;
+      if (c < best_cost) { best_cost = c; split = t.kernel == GK_T64 ? GK_SPLIT64 : GK_SPLIT128; }
+    }
+    if (split != GK_INVALID) return split;
+  }
+  return best->kernel;
 }
 }  // namespace
 
 bool gemm_bf16_can_fuse_key_norms(int64_t m, int n, int k, int qcols, int dh) {
   if (dh != 64 && dh != 80) return false;
   GemmArgs a{};
-  a.m = m; a.n = n; a.k = k; a.lda = k; a.ldc = 2 * qcols; a.epi = EPI_QKV; a.split = 2 * qcols; a.qcols = qcols;
+  a.m = m; a.n = n; a.k = k; a.lda = k; a.ldc = 2 * qcols; a.epi = EPI_QKV; a.split = 2 * qcols; a.qcols = qcols; a.kn_dh = dh;
   int tn = 0, bn = 0;
   const GemmKernel gk = choose_kernel(a, &tn, &bn);
-  if (gk == GK_INVALID || gk == GK_SPLITK) return false;
   // whole heads per wave tile, wave tiles that start at head boundaries, no shifted last tile
-  return tn % dh == 0 && tn / dh <= 4 && qcols % tn == 0 && ((gk != GK_P320 && gk != GK_P256) || n % bn == 0);
+  return gk != GK_INVALID && wave_tile_holds_heads(tn, qcols, dh) && (!is_persistent(gk) || n % bn == 0);
 }
 
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
@@ -866,10 +970,10 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
   int tn = 0, bn = 0;
   const GemmKernel gk = choose_kernel(a, &tn, &bn);
   if (a.epi == EPI_QKV && a.kmax2 &&
-      !(gk != GK_INVALID && (a.kn_dh == 64 || a.kn_dh == 80) && tn % a.kn_dh == 0 && a.qcols % tn == 0 &&
-        a.split == 2 * a.qcols && a.row_seg && ((gk != GK_P320 && gk != GK_P256) || a.n % bn == 0)))
+      !(gk != GK_INVALID && wave_tile_holds_heads(tn, a.qcols, a.kn_dh) && a.split == 2 * a.qcols && a.row_seg &&
+        (!is_persistent(gk) || a.n % bn == 0)))
     return hipErrorInvalidValue;
-  if ((gk == GK_P320 || gk == GK_P256) && a.epi == EPI_RESID && (double)a.m * (double)a.n * 4.0 > 400e6) {
+  if (is_persistent(gk) && a.epi == EPI_RESID && (double)a.m * (double)a.n * 4.0 > 400e6) {
     GemmArgs g = a;                                 // an output larger than the last-level cache: see wave_epilogue
     g.epi = EPI_RESID_AHEAD;
     return gk == GK_P320 ? launch_persist<256, 320, 4, 2>(g, s) : launch_persist<256, 256, 2, 4>(g, s);
@@ -877,18 +981,24 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
   switch (gk) {
     case GK_P320: return launch_persist<256, 320, 4, 2>(a, s);
     case GK_P256: return launch_persist<256, 256, 2, 4>(a, s);
-    case GK_SPLITK: {
+    case GK_SPLIT128:
+    case GK_SPLIT64: {
       GemmArgs g = a;
       g.epi = EPI_PARTIAL; g.ksplit = 4;
-      const hipError_t e = launch_cfg<128, 128, 2, 2, 64, 2, 2>(g, s);
+      const hipError_t e = gk == GK_SPLIT64 ? launch_cfg<64, 64, 2, 2, 1, 3, 3, true>(g, s) : launch_cfg<128, 128, 2, 2, 1, 2, 2, true>(g, s);
       if (e != hipSuccess) return e;
       const int64_t n4 = (int64_t)a.m * (a.n / 4);
       hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s,
                          reinterpret_cast<float*>(a.c), a.ldc, a.partial, a.bias, a.m, a.n, 4);
       return hipGetLastError();
     }
-    case GK_T64: return launch_cfg<64, 64, 1, 2, 64, 2, 4>(a, s);
-    case GK_T128: return launch_cfg<128, 128, 2, 2, 64, 2, 2>(a, s);
+    case GK_T192x256: return launch_cfg<192, 256, 2, 2, 1, 2, 1>(a, s);
+    case GK_T256x160: return launch_cfg<256, 160, 4, 1, 1, 3, 1>(a, s);
+    case GK_T256x128: return launch_cfg<256, 128, 4, 2, 1, 3, 1>(a, s);
+    case GK_T128x160: return launch_cfg<128, 160, 2, 1, 2, 4, 1>(a, s);
+    case GK_T128K2: return launch_cfg<128, 128, 2, 2, 2, 4, 1>(a, s);
+    case GK_T128: return launch_cfg<128, 128, 2, 2, 1, 2, 2>(a, s);
+    case GK_T64: return launch_cfg<64, 64, 2, 2, 1, 3, 3>(a, s);
     default: return hipErrorInvalidValue;
   }
 }

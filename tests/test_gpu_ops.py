@@ -439,3 +439,12 @@ def test_gemm_f32_tile_edges(m, n, k, epi):
 def test_attention_f32_head_sizes(dh):
     """Segments around the 16-query and 16-key tiles and the four waves that share the keys; every remaining head size."""
     test_attention([15, 16, 17, 1, 63, 64, 65, 80], 2 * dh, 2, 3.0 / dh ** 0.5 * 4, "f32")
+
+
+# ragged in both directions; in this order the tiles are 64x64, 128x128 (k shared by two waves), 128x160, 256x128, 256x160,
+# 192x256, 256x256, 256x320, 128x128, with the shortest contractions that each of them is taken for
+@pytest.mark.parametrize("m,n,k", [(239, 816, 64), (837, 3504, 256), (4560, 1096, 320), (6769, 1032, 448), (8671, 1032, 448),
+                                   (8210, 1128, 768), (8490, 1672, 128), (7711, 2248, 192), (8393, 2312, 192)])
+@pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESID])
+def test_gemm_bf16_tile_kernels(m, n, k, epi):
+    test_gemm_bf16(m, n, k, epi)
