@@ -731,11 +731,30 @@ int tcmv_encode(tcmv_ctx* ctx, const tcmv_plan* p, const void* d_meta, const voi
                                           d.pos == TCMV_POS_LEARNED_1D ? reinterpret_cast<const float*>(ctx->w.pos0) : nullptr,
                                           d.d, s); }), "CLS rows");
   }
+  // Slices of the last product that wait in the workspace: the next norm adds them to x first.
+  const float* slices = nullptr;
+  const float* slices_bias = nullptr;
+  auto norm = [&](const float* gm, const float* bt, void* y, int out_bf16) {
+    const float* part = slices;
+    slices = nullptr;
+    return timed(ctx, TCMV_K_LAYERNORM, s, [&] {
+      return part ? launch_layernorm_slices(x, part, slices_bias, gm, bt, y, T, d.d, d.ln_eps, out_bf16, s, d.norm)
+                  : launch_layernorm(x, gm, bt, y, T, d.d, d.ln_eps, out_bf16, s, d.norm); });
+  };
+  // products that accumulate into x; `norm_follows`: the next kernel that touches x is a norm
+  auto accumulate = [&](GemmArgs& g, int cat, bool norm_follows) {
+    if (ws.splitk_bytes) {
+      g.partial = reinterpret_cast<float*>(wsb + ws.splitk);
+      g.defer_reduce = norm_follows;
+      if (norm_follows && gemm_bf16_slices(g) > 1) { slices = g.partial; slices_bias = g.bias; }
+    }
+    return timed(ctx, cat, s, [&] { return run_gemm(ctx, g, s); });
+  };
   for (int l = 0; l < d.layers; ++l) {
     const void* const* L = ctx->layer.data() + (size_t)l * 12;
     auto f = [&](int j) { return reinterpret_cast<const float*>(L[j]); };
     const bool windowed = d.window && !(d.full_every && (l + 1) % d.full_every == 0);
-    TCMV_CHECK(timed(ctx, TCMV_K_LAYERNORM, s, [&] { return launch_layernorm(x, f(0), f(1), xn, T, d.d, d.ln_eps, bf, s, d.norm); }), "LN1");
+    TCMV_CHECK(norm(f(0), f(1), xn, bf), "LN1");
     bool use_kmax = false, kmax_fused = false;
     uint32_t *kmax = nullptr, *kmax_other = nullptr;
     const int32_t* row_seg = nullptr;
@@ -800,9 +819,9 @@ int tcmv_encode(tcmv_ctx* ctx, const tcmv_plan* p, const void* d_meta, const voi
       GemmArgs g{};
       g.a = xn; g.lda = da; g.w = L[4]; g.bias = f(5); g.c = x; g.ldc = d.d; g.m = T; g.n = d.d; g.k = da;
       g.epi = EPI_RESID;
-      TCMV_CHECK(timed(ctx, TCMV_K_OUT_GEMM, s, [&] { return run_gemm(ctx, g, s); }), "out-proj GEMM");
+      TCMV_CHECK(accumulate(g, TCMV_K_OUT_GEMM, true), "out-proj GEMM");
     }
-    TCMV_CHECK(timed(ctx, TCMV_K_LAYERNORM, s, [&] { return launch_layernorm(x, f(6), f(7), xn, T, d.d, d.ln_eps, bf, s, d.norm); }), "LN2");
+    TCMV_CHECK(norm(f(6), f(7), xn, bf), "LN2");
     {
       GemmArgs g{};
       g.a = xn; g.lda = d.d; g.w = L[8]; g.bias = f(9); g.c = hbuf; g.ldc = d.mlp; g.m = T; g.k = d.d;
@@ -814,15 +833,11 @@ int tcmv_encode(tcmv_ctx* ctx, const tcmv_plan* p, const void* d_meta, const voi
       GemmArgs g{};
       g.a = hbuf; g.lda = d.mlp; g.w = L[10]; g.bias = f(11); g.c = x; g.ldc = d.d; g.m = T; g.n = d.d; g.k = d.mlp;
       g.epi = EPI_RESID;
-      if (ws.splitk_bytes) g.partial = reinterpret_cast<float*>(wsb + ws.splitk);
-      TCMV_CHECK(timed(ctx, TCMV_K_FC2_GEMM, s, [&] { return run_gemm(ctx, g, s); }), "fc2 GEMM");
+      TCMV_CHECK(accumulate(g, TCMV_K_FC2_GEMM, l + 1 < d.layers || d.final_ln), "fc2 GEMM");
     }
   }
   if (d.final_ln)
-    TCMV_CHECK(timed(ctx, TCMV_K_LAYERNORM, s, [&] {
-                 return launch_layernorm(x, reinterpret_cast<const float*>(ctx->w.lnf_g),
-                                         reinterpret_cast<const float*>(ctx->w.lnf_b), x, T, d.d, d.ln_eps, 0, s, d.norm); }),
-               "final LN");
+    TCMV_CHECK(norm(reinterpret_cast<const float*>(ctx->w.lnf_g), reinterpret_cast<const float*>(ctx->w.lnf_b), x, 0), "final LN");
   return TCMV_OK;
 }
 

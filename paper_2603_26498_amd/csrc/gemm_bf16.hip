@@ -38,7 +38,7 @@
 // sub-tile, each with half of the k-steps: the wave tiles stay large (64x160: 7 fragment reads for 10 MFMAs) where the
 // workgroup's is small.  4096 x 1280 x 5120: 79 -> 63 us; 256 x 3840 x 1280: 11.8 -> 8.0; 64 x 5120 x 5120: 58 -> 33.
 // A long contraction over few rows that accumulates into the residual stream is cut into four slices of k whose
-// fp32 partial sums a second kernel adds in slice order.
+// fp32 partial sums a second kernel, or the norm that reads the stream next, adds in slice order.
 //
 // Workgroups are numbered so that the eight XCDs (workgroup id mod 8) each walk
 // a contiguous range of tiles: neighbouring tiles share A rows or W rows in the
@@ -881,7 +881,7 @@ enum GemmKernel { GK_INVALID, GK_P320, GK_P256, GK_T192x256, GK_T256x160, GK_T25
 struct TileKernel { GemmKernel kernel; int bm, bn, wave_n, shared; float base, per_k, floor_k; };
 constexpr TileKernel kTileKernels[] = {
     {GK_P256, 256, 256, 64, 0, 5.0f, 1.65f, 0.f},      {GK_P320, 256, 320, 160, 0, 8.0f, 1.75f, 0.f},
-    {GK_T192x256, 192, 256, 128, 0, 8.0f, 1.40f, 0.f}, {GK_T256x160, 256, 160, 160, 0, 9.0f, 1.05f, 0.f},
+    {GK_T192x256, 192, 256, 128, 0, 16.f, 1.35f, 0.f}, {GK_T256x160, 256, 160, 160, 0, 9.0f, 1.05f, 0.f},
     {GK_T256x128, 256, 128, 64, 0, 7.5f, 0.85f, 0.f},  {GK_T128x160, 128, 160, 160, 0, 5.0f, 0.70f, 0.f},
     {GK_T128K2, 128, 128, 64, 0, 3.5f, 0.53f, 0.f},    {GK_T128, 128, 128, 64, 1, 6.0f, 0.55f, 0.80f},
     {GK_T64, 64, 64, 32, 1, 2.0f, 0.22f, 0.36f}};
@@ -939,14 +939,15 @@ GemmKernel choose_kernel(const GemmArgs& a, int* wave_tile_n, int* block_n) {
     if (!best || c < best_cost) { best = &t; best_cost = c; }
   }
   *wave_tile_n = best->wave_n; *block_n = best->bn;
-  // A long contraction over few rows that accumulates (fc2 of one small request): a quarter of k per workgroup, added
-  // to C in a fixed order by a second kernel, where that is estimated to win in spite of it (256 x 1280 x 5120: 16 us
-  // with 64x64 tiles, 30 unsplit; 1120 rows: 34 with 128x128 tiles, 37 unsplit).
-  if (a.epi == EPI_RESID && a.partial && a.k >= 2048 && (a.k / 64) % 4 == 0) {
+  // A contraction over few rows that accumulates (out-projection and fc2 of one small request): a quarter of k per
+  // workgroup, added to C in a fixed order by a second kernel or by the norm that follows (defer_reduce), where that is
+  // estimated to win in spite of it (256 x 1280 x 5120: 12.5 us + 3.9 with 64x64 tiles, 30 unsplit; 1120 rows: 28 + 6.4
+  // with 128x128 tiles, 37 unsplit; 256 x 1280 x 1280: 5.8 against 7.9, 560 rows 8.7 against 8.3).
+  if (a.epi == EPI_RESID && a.partial && a.k >= (a.defer_reduce ? 1024 : 2048) && (a.k / 64) % 4 == 0) {
     GemmKernel split = GK_INVALID;
     for (const TileKernel& t : kTileKernels) {
       if (!t.shared) continue;
-      const float c = tile_cost(t, a.m, a.n, a.k, 4) + 3.9f + 1.75e-6f * (float)a.m * (float)a.n;
+      const float c = tile_cost(t, a.m, a.n, a.k, 4) + (a.defer_reduce ? 2.5f : 5.4f) + 1.75e-6f * (float)a.m * (float)a.n;
       if (c < best_cost) { best_cost = c; split = t.kernel == GK_T64 ? GK_SPLIT64 : GK_SPLIT128; }
     }
     if (split != GK_INVALID) return split;
@@ -963,6 +964,12 @@ bool gemm_bf16_can_fuse_key_norms(int64_t m, int n, int k, int qcols, int dh) {
   const GemmKernel gk = choose_kernel(a, &tn, &bn);
   // whole heads per wave tile, wave tiles that start at head boundaries, no shifted last tile
   return gk != GK_INVALID && wave_tile_holds_heads(tn, qcols, dh) && (!is_persistent(gk) || n % bn == 0);
+}
+
+int gemm_bf16_slices(const GemmArgs& a) {
+  int tn = 0, bn = 0;
+  const GemmKernel gk = choose_kernel(a, &tn, &bn);
+  return gk == GK_SPLIT128 || gk == GK_SPLIT64 ? 4 : 1;
 }
 
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
@@ -986,7 +993,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
       GemmArgs g = a;
       g.epi = EPI_PARTIAL; g.ksplit = 4;
       const hipError_t e = gk == GK_SPLIT64 ? launch_cfg<64, 64, 2, 2, 1, 3, 3, true>(g, s) : launch_cfg<128, 128, 2, 2, 1, 2, 2, true>(g, s);
-      if (e != hipSuccess) return e;
+      if (e != hipSuccess || a.defer_reduce) return e;
       const int64_t n4 = (int64_t)a.m * (a.n / 4);
       hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s,
                          reinterpret_cast<float*>(a.c), a.ldc, a.partial, a.bias, a.m, a.n, 4);

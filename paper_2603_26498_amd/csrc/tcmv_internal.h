@@ -83,6 +83,9 @@ struct GemmArgs {
   // room for 4 * m * n values) the launcher may cut k into 4 slices computed by 4 times as many workgroups
   // and add the slices to C in slice order in a second kernel (same result from run to run)
   float* partial; int ksplit;
+  // the slices stay in `partial` when the launcher cuts k (gemm_bf16_slices says whether it will): the caller hands
+  // them to launch_layernorm_slices
+  int defer_reduce;
 };
 
 struct AttnArgs {
@@ -124,8 +127,12 @@ bool preprocess_has_strip_kernel(int patch, int tpatch);
 // rms != 0: RMSNorm (no mean subtraction, b is not read)
 hipError_t launch_layernorm(const float* x, const float* g, const float* b, void* y, int64_t rows, int d,
                             float eps, int out_bf16, hipStream_t s, int rms = 0);
+// x[r] += bias + slice 0 + .. + slice 3 of partial[4][rows][d] first (written back when y is another buffer: bf16 output)
+hipError_t launch_layernorm_slices(float* x, const float* partial, const float* bias, const float* g, const float* b, void* y,
+                                   int64_t rows, int d, float eps, int out_bf16, hipStream_t s, int rms);
 hipError_t launch_stream_ref(const void* in, size_t in_bytes, void* out, size_t out_bytes, hipStream_t s);
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
+int gemm_bf16_slices(const GemmArgs& a);   // slices of k that launch_gemm_bf16 computes separately (1 or 4)
 // true when launch_gemm_bf16 computes the key-norm maxima in the epilogue of an m x n x k QKV projection whose key
 // columns are [qcols, 2 qcols) with heads of dh columns (the wave tiles must line up with the heads)
 bool gemm_bf16_can_fuse_key_norms(int64_t m, int n, int k, int qcols, int dh);

@@ -270,3 +270,24 @@ def test_single_small_request_with_long_mlp_contraction():
     torch.cuda.synchronize()
     n = hidden.shape[0]
     assert_tokens_close(hb[:n].cpu().numpy(), hidden.cpu().numpy().astype(np.float64), 2e-3, 0.99999, "batch vs alone")
+
+
+@pytest.mark.parametrize("h,w,rms,final_ln", [(224, 224, 0, 0), (224, 224, 0, 1), (196, 252, 1, 0), (196, 252, 1, 1), (420, 504, 0, 1)])
+def test_products_cut_along_k_and_added_by_the_norm(h, w, rms, final_ln):
+    """One small image through full-width layers: the products that accumulate are computed in four slices of k, which
+    the following norm (or, behind the last layer, a kernel of its own) adds to the residual stream; 256, 252 and 1080
+    tokens, LayerNorm and RMSNorm, with and without a final norm."""
+    import dataclasses
+    if rms:
+        desc = dataclasses.replace(workloads.windowed_desc(layers=2, d=1280, heads=16, mlp=5120, out_dim=0, window=8, full_every=2), merge=2)
+    else:
+        desc = workloads.qwen_like_desc(layers=2, d=1280, heads=16, mlp=5120, out_dim=0, max_grid=48)
+    desc = dataclasses.replace(desc, final_ln=final_ln)
+    rng = np.random.default_rng(h * w + rms + final_ln)
+    items = [workloads.Item(workloads.IMAGE, 1, h, w, h, w, workloads.random_frames(rng, 1, h, w))]
+    wl = workloads.Workload("slices", desc, items, workloads.make_weights(desc, 3, random_affine=True))
+    for key, x in wl.weights.items():
+        wl.weights[key] = workloads.snap_to_bf16_grid(x)
+    ref = oracle.run(wl)
+    _, _, _, hidden, _ = run_gpu(wl)
+    assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, "hidden")
