@@ -919,7 +919,12 @@ GemmKernel choose_kernel(const GemmArgs& a, int* wave_tile_n, int* block_n) {
       const int64_t t = ((a.m + bm - 1) / bm) * ((a.n + bn - 1) / bn);
       return ((t + 255) / 256) * bm * bn;
     };
-    if (area(256, 320) <= area(256, 256)) { *wave_tile_n = 160; *block_n = 320; return GK_P320; }
+    const int64_t wide = area(256, 320), square = area(256, 256);
+    // at the same area, the one whose wave tiles hold whole heads where key norms are wanted: the separate pass over the
+    // keys takes 21 us at 25772 rows with heads of 64, the square tiles 10 - 15 more than the 184 of the wide ones
+    const bool norms = a.epi == EPI_QKV && a.kn_dh && wide == square && a.n % 256 == 0 && wave_tile_holds_heads(64, a.qcols, a.kn_dh) &&
+                       !wave_tile_holds_heads(160, a.qcols, a.kn_dh);
+    if (wide <= square && !norms) { *wave_tile_n = 160; *block_n = 320; return GK_P320; }
     *wave_tile_n = 64; *block_n = 256;
     return GK_P256;
   }
