@@ -84,8 +84,8 @@ int fail_hip(tcmv_ctx* ctx, hipError_t e, const char* what) {
 // CU instead of twice and are used when rounding the segments up to 512 rows wastes little.
 int attn_bq_bf16(int dh, int heads, const std::vector<int64_t>& seg_len) {
   if (dh > 80) return 128;
-  int64_t rows = 0, padded = 0, items256 = 0;
-  for (int64_t n : seg_len) { rows += n; padded += (n + 511) / 512 * 512; items256 += (n + 255) / 256; }
+  int64_t rows = 0, padded = 0, items256 = 0, items512 = 0;
+  for (int64_t n : seg_len) { rows += n; padded += (n + 511) / 512 * 512; items256 += (n + 255) / 256; items512 += (n + 511) / 512; }
   // a single small request: fewer 256-row work items than CUs; 128-row items double the workgroups
   if (items256 * heads < 256) return 128;
   // segments that fill their last 256-row item badly (576 tokens: 3 items for 2.25 items' worth of rows): 128-row
@@ -93,6 +93,8 @@ int attn_bq_bf16(int dh, int heads, const std::vector<int64_t>& seg_len) {
   int64_t p256 = 0, p128 = 0;
   for (int64_t n : seg_len) { p256 += (n + 255) / 256 * 256; p128 += (n + 127) / 128 * 128; }
   if (rows > 0 && p256 * 100 > rows * 115 && p128 * 100 <= p256 * 90) return 128;
+  // fewer 512-row items than CUs leave CUs idle: twice as many 256-row items (4096 tokens, 16 heads: 108 -> 76 us)
+  if (items512 * heads < 256) return 256;
   return (rows > 0 && padded * 100 <= rows * 103) ? 512 : 256;
 }
 

@@ -448,3 +448,10 @@ def test_attention_f32_head_sizes(dh):
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESID])
 def test_gemm_bf16_tile_kernels(m, n, k, epi):
     test_gemm_bf16(m, n, k, epi)
+
+
+@pytest.mark.parametrize("lens,qs,big_head", [([4096, 2048, 2048], 6.0, None), ([4096, 4096], 1.0, 3)])
+def test_attention_work_items_of_512_rows(lens, qs, big_head):
+    """16 items of 512 rows for 16 heads, the fewest that fill 256 CUs: peaked scores, and the reference-free copy for all
+    heads but one (fewer items are cut into 256 rows)."""
+    test_attention_large_work_items(lens, qs, big_head)
