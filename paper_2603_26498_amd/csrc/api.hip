@@ -524,7 +524,10 @@ int tcmv_plan_create(tcmv_ctx* ctx, const tcmv_item* items, int n_items, tcmv_pl
     for (int64_t n : len) { rows += (double)n; pairs += (double)n * (double)n; }
     return rows > 0 && pairs >= 1024.0 * rows;
   };
-  p->norm_bound = d.dtype == TCMV_BF16 && long_enough(seg_len);
+  // A small request (128-row items that do not give every CU two workgroups) waits for memory and barriers rather than for
+  // the vector unit: the reference-free loop saves 0.7 us at 1120 tokens (23.8 against 24.5) and the second launch costs 4.6.
+  const bool small_request = p->bq == 128 && (int64_t)p->work.size() * d.heads < 512;
+  p->norm_bound = d.dtype == TCMV_BF16 && !small_request && long_enough(seg_len);
   p->norm_bound_win = d.dtype == TCMV_BF16 && long_enough(win_len);
   p->n_windows = (int)win_start.size();
   for (int64_t n : win_len) p->max_win_len = std::max(p->max_win_len, n);
