@@ -221,8 +221,13 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const float* vp = V + (size_t)(w.seg_start + min(j0 + 4 * lg + v, w.seg_len - 1)) * a.ldv + lr;
+      // zero past the end of the segment: the last row, which is read there, may hold an infinity, and 0 * inf is NaN
+      const bool key = j0 + 4 * lg + v < w.seg_len;
 #pragma unroll
-      for (int i = 0; i < ND; ++i) vf[v][i] = vp[16 * i];
+      for (int i = 0; i < ND; ++i) {
+        const float x = vp[16 * i];
+        vf[v][i] = key ? x : 0.f;
+      }
     }
     f32v4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -237,9 +242,11 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mn = fmaxf(m, mx);                   // finite: the tile holds at least one key
-    const float al = expf(m - mn);
-    m = mn;
+    const float m_old = m;
+    m = fmaxf(m, mx);
+    // -inf as long as all scores are: such keys weigh nothing (exp(-inf - 0) = 0, not exp(-inf + inf))
+    const float mn = m == -INFINITY ? 0.f : m;
+    const float al = expf(m_old - mn);
     l *= al;
 #pragma unroll
     for (int i = 0; i < ND; ++i) o[i] *= al;
@@ -257,7 +264,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
   for (int i = 0; i < ND; ++i) *reinterpret_cast<f32v4*>(&so[wave][lr][16 * i + 4 * lg]) = o[i];
   if (lg == 0) { sm[wave][lr] = m; sl[wave][lr] = l; }
   __syncthreads();
-  // waves that saw no key hold m = -inf, l = 0, o = 0: their weight is exp(-inf) = 0
+  // waves that saw no key, or only scores of -inf, hold m = -inf, l = 0, o = 0: their weight is exp(-inf) = 0
   for (int e = tid; e < BQ * DH; e += 256) {
     const int r = e / DH, c = e - r * DH;
     if (r >= w.nq) break;

@@ -441,6 +441,31 @@ def test_attention_f32_head_sizes(dh):
     test_attention([15, 16, 17, 1, 63, 64, 65, 80], 2 * dh, 2, 3.0 / dh ** 0.5 * 4, "f32")
 
 
+@pytest.mark.parametrize("dh", [16, 64])
+def test_attention_f32_infinities_stay_where_they_belong(dh):
+    """An infinite value in the last row of V reaches its own column only, although the last tile of keys is padded
+    with that row; keys that score -inf weigh nothing, also where they fill the first tile of 16 keys that a wave sees
+    (keys 16..31 of 80, 0..15 of 40).  A row whose keys all score -inf has no softmax."""
+    rng = np.random.default_rng(dh)
+    lens, heads = [17, 80, 40, 20], 2
+    d = heads * dh
+    cu = [0] + [int(c) for c in np.cumsum(lens)]
+    qkv = _qkv(rng, cu[-1], d, 1.0, "f32")
+    qkv[:, 0] = 1.0 + np.abs(qkv[:, 0])                    # first element of the first head's queries: positive
+    qkv[16, 2 * d + 3] = np.inf                             # segment of 17: V of the last row
+    qkv[cu[1] + 16:cu[1] + 32, d] = -np.inf                 # segment of 80: scores of the first head
+    qkv[cu[2]:cu[2] + 16, d] = -np.inf                      # segment of 40
+    qkv[cu[3]:cu[4], d] = -np.inf                           # segment of 20: every key
+    x = qkv.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        ref = oe.attention(x[:, :d], x[:, d:2 * d], x[:, 2 * d:], cu, heads)
+    got = _attn("f32", qkv, cu, d, heads)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(ref[cu[3]:, :dh]).all() and np.isnan(ref).sum() == 20 * dh
+    assert np.array_equal(np.isinf(got), np.isinf(ref)) and np.isinf(ref).sum() == 17
+    ok = np.isfinite(ref)
+    assert np.abs(got[ok] - ref[ok]).max() <= 2e-5 * max(1.0, np.abs(ref[ok]).max())
+
+
 # ragged in both directions; in this order the tiles are 64x64, 128x128 (k shared by two waves), 128x160, 256x128, 256x160,
 # 192x256, 256x256, 256x320, 128x128, with the shortest contractions that each of them is taken for
 @pytest.mark.parametrize("m,n,k", [(239, 816, 64), (837, 3504, 256), (4560, 1096, 320), (6769, 1032, 448), (8671, 1032, 448),
