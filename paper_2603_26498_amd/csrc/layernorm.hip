@@ -12,6 +12,10 @@
 
 namespace tcmv {
 
+// Sum of the squares of four values, the products paired in one written-out way: left to the compiler, the pairing (and
+// with it the last bit of the sum) changes with the code around it.
+__device__ __forceinline__ float square_sum(const float4& v) { return fmaf(v.x, v.x, v.y * v.y) + fmaf(v.z, v.z, v.w * v.w); }
+
 template <int NV, bool OUT_BF16, bool RMS>
 __global__ __launch_bounds__(256) void layernorm_kernel(const float* x, const float* __restrict__ gamma,
                                                         const float* __restrict__ beta, void* y,
@@ -40,7 +44,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float* x, const fl
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     v[j].x -= mean; v[j].y -= mean; v[j].z -= mean; v[j].w -= mean;
-    q += lane + 64 * j < nvec ? (v[j].x * v[j].x + v[j].y * v[j].y) + (v[j].z * v[j].z + v[j].w * v[j].w) : 0.f;
+    q += lane + 64 * j < nvec ? square_sum(v[j]) : 0.f;
   }
   const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)d + eps);
 #pragma unroll
@@ -130,7 +134,7 @@ __global__ __launch_bounds__(256) void layernorm_slices_kernel(float* x, const f
   for (int j = 0; j < NV; ++j)
     if (tid + 256 * j < nvec) {
       v[j].x -= mean; v[j].y -= mean; v[j].z -= mean; v[j].w -= mean;
-      q += (v[j].x * v[j].x + v[j].y * v[j].y) + (v[j].z * v[j].z + v[j].w * v[j].w);
+      q += square_sum(v[j]);
     }
   q = wave_sum(q);
   if (lane == 0) sums[1][wave] = q;

@@ -356,6 +356,29 @@ def test_rmsnorm(rows, d, dtype):
     assert np.abs(got - ref).max() <= tol * max(1.0, np.abs(ref).max())
 
 
+@pytest.mark.parametrize("rows,d", [(64, 1280), (33, 1024), (5, 320)])
+def test_rmsnorm_adds_in_one_written_out_order(rows, d):
+    """Results do not change with the compiler's choices: the squares of four neighbours are added as
+    fma(x, x, y*y) + fma(z, z, w*w), a lane adds its groups (64 lanes apart) in order, the lanes are added pairwise."""
+    rng = np.random.default_rng(d)
+    x = rng.normal(0.5, 3, (rows, d)).astype(np.float32)
+    g = (1 + rng.normal(0, 0.3, d)).astype(np.float32)
+    y = torch.empty((rows, d), dtype=torch.float32, device=DEV)
+    B.tcmv_op_layernorm(B.TCMV_F32, dev(x), dev(g), None, y, rows, d, 1e-6)
+    sync()
+    v = x.reshape(rows, d // 4, 4)
+    sq = lambda a, b: (a.astype(np.float64) ** 2 + (b * b).astype(np.float64)).astype(np.float32)   # fma: one rounding
+    q4 = sq(v[..., 0], v[..., 1]) + sq(v[..., 2], v[..., 3])
+    q4 = np.concatenate([q4, np.zeros((rows, -(d // 4) % 64), np.float32)], 1).reshape(rows, -1, 64)
+    q = np.zeros((rows, 64), np.float32)
+    for j in range(q4.shape[1]):
+        q = q + q4[:, j]
+    while q.shape[1] > 1:
+        q = q[:, :q.shape[1] // 2] + q[:, q.shape[1] // 2:]
+    rstd = np.float32(1) / np.sqrt(q / np.float32(d) + np.float32(1e-6))
+    assert np.array_equal(y.cpu().numpy(), x * rstd * g)
+
+
 @pytest.mark.parametrize("m,n2,k", [(300, 256, 128), (1029, 1280, 320), (4100, 6912, 1280)])
 def test_gated_epilogue(m, n2, k):
     """Columns arrive as (gate, up) pairs; the kernel writes silu(gate) * up."""
