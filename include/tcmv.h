@@ -306,6 +306,9 @@ int tcmv_op_gemm(int dtype, int epilogue, const void *d_a, const void *d_w, cons
  * tcmv_op_attention_workspace (0 from the size queries = invalid arguments). */
 size_t tcmv_op_attention_workspace(int dtype, const int64_t *cu_seqlens, int n_seg, int d, int heads);
 size_t tcmv_op_attention_index_bytes(int dtype, const int64_t *cu_seqlens, int n_seg, int d, int heads);
+/* Query rows of a work item (a workgroup) that these segment lengths are cut into, in the operator and in the
+ * encoder's full-attention layers: for tests and for reading profiles.  Host only; 0 = invalid arguments. */
+int tcmv_op_attention_rows(int dtype, const int64_t *cu_seqlens, int n_seg, int d, int heads);
 int tcmv_op_attention_index(int dtype, const int64_t *cu_seqlens, int n_seg, int d, int heads, void *h_index,
                             size_t index_bytes);
 int tcmv_op_attention(int dtype, const void *d_qkv, const int64_t *cu_seqlens, int n_seg, int d, int heads,

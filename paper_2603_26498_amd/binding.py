@@ -86,6 +86,7 @@ SIGNATURES = {
                                C.c_int, C.c_void_p]),
     "tcmv_op_attention_workspace": (C.c_size_t, [C.c_int, C.POINTER(C.c_int64), C.c_int, C.c_int, C.c_int]),
     "tcmv_op_attention_index_bytes": (C.c_size_t, [C.c_int, C.POINTER(C.c_int64), C.c_int, C.c_int, C.c_int]),
+    "tcmv_op_attention_rows": (C.c_int, [C.c_int, C.POINTER(C.c_int64), C.c_int, C.c_int, C.c_int]),
     "tcmv_op_attention_index": (C.c_int, [C.c_int, C.POINTER(C.c_int64), C.c_int, C.c_int, C.c_int, C.c_void_p,
                                           C.c_size_t]),
     "tcmv_op_attention": (C.c_int, [C.c_int, C.c_void_p, C.POINTER(C.c_int64), C.c_int, C.c_int, C.c_int, C.c_void_p,
@@ -286,6 +287,11 @@ def tcmv_op_attention_workspace(dtype, cu_seqlens, d, heads):
     n = len(cu_seqlens) - 1
     arr = (C.c_int64 * (n + 1))(*cu_seqlens)
     return lib().tcmv_op_attention_workspace(dtype, arr, n, d, heads)
+
+
+def tcmv_op_attention_rows(dtype, cu_seqlens, d, heads):
+    n = len(cu_seqlens) - 1
+    return lib().tcmv_op_attention_rows(dtype, (C.c_int64 * (n + 1))(*cu_seqlens), n, d, heads)
 
 
 def tcmv_op_attention_index(dtype, cu_seqlens, d, heads) -> bytes:

@@ -93,8 +93,11 @@ int attn_bq_bf16(int dh, int heads, const std::vector<int64_t>& seg_len) {
   int64_t p256 = 0, p128 = 0;
   for (int64_t n : seg_len) { p256 += (n + 255) / 256 * 256; p128 += (n + 127) / 128 * 128; }
   if (rows > 0 && p256 * 100 > rows * 115 && p128 * 100 <= p256 * 90) return 128;
-  // fewer 512-row items than CUs leave CUs idle: twice as many 256-row items (4096 tokens, 16 heads: 108 -> 76 us)
-  if (items512 * heads < 256) return 256;
+  // Fewer 512-row items than CUs leave CUs idle; 256-row items help as long as every one has a CU of its own (heads of 80:
+  // 4096 tokens x 16 heads 110 -> 82 us).  From two on a CU on they stage every tile twice for the same rows and lose
+  // (4608 tokens 123 us with 512 rows, 133 with 256; 6144 tokens 198 / 203), except with the smaller tiles of smaller
+  // heads (heads of 64: 5120 tokens 142 / 137, 6144 tokens 178 / 175).
+  if (items512 * heads < 256 && (dh < 80 || items256 * heads <= 256)) return 256;
   return (rows > 0 && padded * 100 <= rows * 103) ? 512 : 256;
 }
 
@@ -1039,6 +1042,11 @@ size_t tcmv_op_attention_workspace(int dtype, const int64_t* cu_seqlens, int n_s
 size_t tcmv_op_attention_index_bytes(int dtype, const int64_t* cu_seqlens, int n_seg, int d, int heads) {
   if (!op_attn_args_ok(dtype, cu_seqlens, n_seg, d, heads)) return 0;
   return op_attn_layout(dtype, cu_seqlens, n_seg, d, heads, nullptr, nullptr).index_total;
+}
+
+int tcmv_op_attention_rows(int dtype, const int64_t* cu_seqlens, int n_seg, int d, int heads) {
+  if (!op_attn_args_ok(dtype, cu_seqlens, n_seg, d, heads)) return 0;
+  return op_attn_layout(dtype, cu_seqlens, n_seg, d, heads, nullptr, nullptr).bq;
 }
 
 int tcmv_op_attention_index(int dtype, const int64_t* cu_seqlens, int n_seg, int d, int heads, void* h_index, size_t index_bytes) {

@@ -218,3 +218,15 @@ def test_windowed_plan_whose_transposed_values_do_not_fit_32_bit_offsets_is_refu
         enc.plan(items, upload=False)
     assert e.value.code == B.TCMV_E_BAD_SHAPE and "transposed" in str(e.value)
     assert enc.plan(items[:1000], upload=False).info.n_tokens == 1000 * 64
+
+
+# rows per work item that were measured to be the fastest of 256 and 512 (the choice between them), and the limits of the rule
+@pytest.mark.parametrize("heads,dh,lens,rows", [
+    (16, 80, [4096], 256), (16, 80, [1024] * 4, 256), (8, 80, [8192], 256),               # one 256-row item per CU
+    (16, 80, [4608], 512), (16, 80, [5120], 512), (16, 80, [6144], 512), (16, 80, [7680], 512), (16, 80, [8192], 512),
+    (16, 80, [1024] * 6, 512), (16, 80, [1024, 1024, 5120], 512), (8, 80, [9728], 512),
+    (16, 64, [5120], 256), (16, 64, [6144], 256), (16, 64, [8192], 512), (16, 32, [6144], 256),
+    (16, 80, [3840], 128), (16, 80, [4352], 256), (16, 96, [8192], 128)])
+def test_rows_of_an_attention_work_item(heads, dh, lens, rows):
+    cu = [0] + [int(c) for c in np.cumsum(lens)]
+    assert B.tcmv_op_attention_rows(B.TCMV_BF16, cu, heads * dh, heads) == rows

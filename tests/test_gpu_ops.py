@@ -189,14 +189,15 @@ def test_attention(lens, d, heads, qs, dtype):
         assert np.sqrt(((got - ref) ** 2).mean()) <= 4e-3 * np.sqrt((ref ** 2).mean())
 
 
-@pytest.mark.parametrize("lens,qs,big_head", [
-    ([1000, 333, 1, 0, 640, 257, 129, 2048], 6.0, None),     # ragged: 256-row work items (4 waves x 2 query tiles), peaked
-    ([2048, 2048, 1024], 6.0, None),                          # multiples of 512: 512-row work items (8 waves), peaked
-    ([4096, 3072], 1.0, 3),                                   # long segments: key-norm bound holds except for one head
-    ([1000, 333, 2085, 640, 1500, 64], 1.0, None),            # small scores, ragged: the reference-free loop with masked last tiles
-    ([4096, 2560, 1536], 0.5, None),                          # small scores, full tiles, 512-row items: the reference-free loop without masks
+@pytest.mark.parametrize("lens,qs,big_head,rows", [
+    ([1000, 333, 1, 0, 640, 257, 129, 2048], 6.0, None, 256), # ragged: 256-row work items (4 waves x 2 query tiles), peaked
+    ([2048, 2048, 1024], 6.0, None, 512),                     # multiples of 512: 512-row work items (8 waves), peaked
+    ([4096, 3072], 1.0, 3, 512),                              # long segments: key-norm bound holds except for one head
+    ([4096], 1.0, 3, 256),                                    # the same with as many 256-row items as CUs
+    ([1000, 333, 2085, 640, 1500, 64], 1.0, None, 256),       # small scores, ragged: the reference-free loop with masked last tiles
+    ([4096, 2560, 1536], 0.5, None, 512),                     # small scores, full tiles, 512-row items: the reference-free loop without masks
 ])
-def test_attention_large_work_items(lens, qs, big_head):
+def test_attention_large_work_items(lens, qs, big_head, rows):
     """Enough work items for the kernels with two query tiles per wave to be chosen (a single small problem
     gets 128-row items): 16 heads of 80, ragged and aligned segments, peaked scores (rescaling path), and long
     segments on which the reference-free copy handles all heads but one."""
@@ -204,6 +205,7 @@ def test_attention_large_work_items(lens, qs, big_head):
     d, heads, dh = 1280, 16, 80
     cu = [0] + list(np.cumsum(lens))
     T = cu[-1]
+    assert B.tcmv_op_attention_rows(B.TCMV_BF16, [int(c) for c in cu], d, heads) == rows
     q = rng.normal(0, qs, (T, d)); k = rng.normal(0, 1, (T, d)); v = rng.normal(0, 1, (T, d))
     if big_head is not None:
         q[:, big_head * dh:(big_head + 1) * dh] *= 8.0
@@ -500,6 +502,5 @@ def test_gemm_bf16_tile_kernels(m, n, k, epi):
 
 @pytest.mark.parametrize("lens,qs,big_head", [([4096, 2048, 2048], 6.0, None), ([4096, 4096], 1.0, 3)])
 def test_attention_work_items_of_512_rows(lens, qs, big_head):
-    """16 items of 512 rows for 16 heads, the fewest that fill 256 CUs: peaked scores, and the reference-free copy for all
-    heads but one (fewer items are cut into 256 rows)."""
-    test_attention_large_work_items(lens, qs, big_head)
+    """16 items of 512 rows for 16 heads, one for every CU: peaked scores, and the reference-free copy for all heads but one."""
+    test_attention_large_work_items(lens, qs, big_head, 512)
