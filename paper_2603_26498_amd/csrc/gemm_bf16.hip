@@ -341,9 +341,11 @@ __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[MI][NI], const GemmA
 }
 
 
-// waits until at most N vector-memory loads of this wave are in flight and its LDS reads are back
+// Waits until at most N vector-memory loads of this wave are in flight and its LDS reads are back, then for the other
+// waves of the workgroup.  One block, so that nothing moves in between, and not __syncthreads: before that barrier the
+// compiler drained all loads in the prologue and in the last iterations.
 template <int N>
-__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
+__device__ __forceinline__ void wait_loads_and_waves() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory"); }
 
 template <int BM, int BN, int WM, int WN, int KW, int NSTAGE, int MINB, int EPI>
 __global__ __launch_bounds__(WM* WN* KW * 64, MINB) void gemm_bf16_kernel(GemmArgs g) {
@@ -466,9 +468,9 @@ __global__ __launch_bounds__(WM* WN* KW * 64, MINB) void gemm_bf16_kernel(GemmAr
 #pragma unroll
   for (int i = 0; i < NSTAGE; ++i)
     if (i < nk) load_tiles(i, i);
-  if (nk >= NSTAGE) wait_loads<(NSTAGE - 1) * NL>();
-  else wait_loads<0>();
-  __syncthreads();                     // tile 0 visible to all waves
+  if (nk >= NSTAGE) wait_loads_and_waves<(NSTAGE - 1) * NL>();
+  else wait_loads_and_waves<0>();
+  // tile 0 is visible to all waves
   frags(0, 0, 0);
   // REST: k-tiles behind this one, NSTAGE standing for "at least NSTAGE" (tile kt+NSTAGE is then requested)
   auto iteration = [&](int kt, int cur, auto rest_c) {
@@ -491,8 +493,7 @@ __global__ __launch_bounds__(WM* WN* KW * 64, MINB) void gemm_bf16_kernel(GemmAr
       }
     }
     if (REST >= 1) {
-      wait_loads<(REST >= NSTAGE ? NSTAGE - 2 : REST - 1) * NL>();
-      __syncthreads();
+      wait_loads_and_waves<(REST >= NSTAGE ? NSTAGE - 2 : REST - 1) * NL>();
       if (REST == NSTAGE) load_tiles(kt + NSTAGE, cur);
       frags(next, 0, 0);
     }
