@@ -228,6 +228,14 @@ const int64_t *tcmv_plan_cu_seqlens(const tcmv_plan *plan);
  * Returns the number of entries, or a negative error. */
 int64_t tcmv_plan_row_map(const tcmv_plan *plan, int which, const int32_t **out);
 
+/* Which kernels the sizes of a plan lead to, for tests and for reading profiles (host only, nothing is launched).
+ * tcmv_plan_key_norms: whether attention of this layer uses key norms: 0 no, 1 from a pass of their own, 2 from the
+ * QKV product (or a negative error).  tcmv_plan_gemm_kernel: name of the bf16 kernel of a layer's product (kernel_class
+ * TCMV_K_QKV_GEMM, _OUT_GEMM, _FC1_GEMM or _FC2_GEMM): tile rows x columns, then "persistent" (one workgroup per CU),
+ * "k/2" (two waves share the k-steps of a sub-tile) or "slices" (four slices of k); NULL for fp32 models and errors. */
+int tcmv_plan_key_norms(const tcmv_plan *plan, int layer);
+const char *tcmv_plan_gemm_kernel(const tcmv_plan *plan, int kernel_class, int layer);
+
 /* Stage 1 (Sec. 2.1: visual inputs are first preprocessed into pixels or frames;
  * Sec. 3.2 times this stage per request): resize + normalise + patchify in one
  * pass.  d_meta: the device copy of the plan's metadata.  d_patches
@@ -294,6 +302,9 @@ int tcmv_op_stream(const void *d_in, size_t in_bytes, void *d_out, size_t out_by
  * silu(column 2j) * column 2j+1, d_c is bf16 [m, n/2].  bias fp32 [n] or NULL. */
 int tcmv_op_gemm(int dtype, int epilogue, const void *d_a, const void *d_w, const float *d_bias,
                  void *d_c, int64_t m, int n, int k, void *stream);
+
+/* Name of the kernel that tcmv_op_gemm takes for a bf16 product of these sizes (as tcmv_plan_gemm_kernel; host only). */
+const char *tcmv_op_gemm_kernel(int epilogue, int64_t m, int n, int k);
 
 /* Block-diagonal bidirectional attention.  d_qkv [T, 3*d] (q | k | v thirds,
  * head j = columns [j*dh, (j+1)*dh) of each third), bf16 or fp32; cu_seqlens:

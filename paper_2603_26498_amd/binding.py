@@ -72,6 +72,8 @@ SIGNATURES = {
     "tcmv_plan_row_map": (C.c_int64, [C.c_void_p, C.c_int, C.POINTER(C.POINTER(C.c_int32))]),
     "tcmv_plan_meta": (C.c_void_p, [C.c_void_p, C.POINTER(C.c_size_t)]),
     "tcmv_plan_upload": (C.c_int, [C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
+    "tcmv_plan_key_norms": (C.c_int, [C.c_void_p, C.c_int]),
+    "tcmv_plan_gemm_kernel": (C.c_char_p, [C.c_void_p, C.c_int, C.c_int]),
     "tcmv_preprocess": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
     "tcmv_encode": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t,
                               C.c_void_p]),
@@ -84,6 +86,7 @@ SIGNATURES = {
     "tcmv_op_stream": (C.c_int, [C.c_void_p, C.c_size_t, C.c_void_p, C.c_size_t, C.c_void_p]),
     "tcmv_op_gemm": (C.c_int, [C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_int,
                                C.c_int, C.c_void_p]),
+    "tcmv_op_gemm_kernel": (C.c_char_p, [C.c_int, C.c_int64, C.c_int, C.c_int]),
     "tcmv_op_attention_workspace": (C.c_size_t, [C.c_int, C.POINTER(C.c_int64), C.c_int, C.c_int, C.c_int]),
     "tcmv_op_attention_index_bytes": (C.c_size_t, [C.c_int, C.POINTER(C.c_int64), C.c_int, C.c_int, C.c_int]),
     "tcmv_op_attention_rows": (C.c_int, [C.c_int, C.POINTER(C.c_int64), C.c_int, C.c_int, C.c_int]),
@@ -281,6 +284,23 @@ def tcmv_op_gemm(dtype, epilogue, d_a, d_w, d_bias, d_c, m, n, k, stream=None):
     rc = lib().tcmv_op_gemm(dtype, epilogue, _ptr(d_a), _ptr(d_w), _ptr(d_bias), _ptr(d_c), m, n, k, stream)
     if rc != TCMV_OK:
         raise TcmvError(rc, "tcmv_op_gemm")
+
+
+def _name(s):
+    return s.decode() if s else None
+
+
+def tcmv_op_gemm_kernel(epilogue, m, n, k):
+    return _name(lib().tcmv_op_gemm_kernel(epilogue, m, n, k))
+
+
+def tcmv_plan_gemm_kernel(plan, kernel_class, layer=0):
+    """kernel_class: an entry of KERNEL_CLASSES."""
+    return _name(lib().tcmv_plan_gemm_kernel(plan, KERNEL_CLASSES.index(kernel_class), layer))
+
+
+def tcmv_plan_key_norms(plan, layer=0):
+    return lib().tcmv_plan_key_norms(plan, layer)
 
 
 def tcmv_op_attention_workspace(dtype, cu_seqlens, d, heads):

@@ -186,7 +186,7 @@ EncodeWs encode_ws(const tcmv_plan* p) {
   // of the next.
   w.kmax_bytes = align_up(((size_t)std::max(p->n_segments, p->n_windows) * d.heads + 1) * kKmaxStride * 4, 256);
   w.kmax = off; off += d.dtype == TCMV_BF16 ? 2 * w.kmax_bytes : 0;
-  // one small request: room for the four k-slices of the fc2 product (see GemmArgs::partial)
+  // one small request: room for the four k-slices of the products that accumulate (see GemmArgs::partial)
   const bool few_rows = d.dtype == TCMV_BF16 && ((T + 127) / 128) * (((size_t)d.d + 127) / 128) < 200;
   w.splitk_bytes = few_rows ? align_up(4 * T * (size_t)d.d * sizeof(float), 256) : 0;
   w.splitk = off; off += w.splitk_bytes;
@@ -264,6 +264,50 @@ hipError_t timed(tcmv_ctx* ctx, int cat, hipStream_t s, F&& launch) {
   if (e != hipSuccess) { ctx->free_spans.push_back(sp); return e; }
   ctx->spans.push_back(sp);
   return hipSuccess;
+}
+
+// How layer `l` attends: inside windows (short ones have a kernel of their own), with key norms or without, and whether
+// the QKV product computes them.
+struct LayerAttn { bool windowed, short_windows, key_norms, fused; };
+LayerAttn layer_attn(const tcmv_plan* p, int l) {
+  const tcmv_model_desc& d = p->ctx->desc;
+  LayerAttn a{};
+  a.windowed = d.window && !(d.full_every && (l + 1) % d.full_every == 0);
+  a.short_windows = a.windowed && p->max_win_len <= 64;
+  a.key_norms = d.dtype == TCMV_BF16 && !a.short_windows && (a.windowed ? p->norm_bound_win : p->norm_bound);
+  a.fused = a.key_norms && gemm_bf16_can_fuse_key_norms(p->n_tokens, 3 * attn_width_of(d), d.d, attn_width_of(d), head_dim_of(d));
+  return a;
+}
+
+// Sizes and epilogue of a product of layer `l` (TCMV_K_QKV_GEMM .. TCMV_K_FC2_GEMM): everything the launcher chooses its
+// kernel by but the presence of `partial`.  The stage call adds the pointers.
+GemmArgs layer_product(const tcmv_plan* p, int kernel_class, int l) {
+  const tcmv_model_desc& d = p->ctx->desc;
+  const bool bf = d.dtype == TCMV_BF16;
+  const int da = attn_width_of(d);               // width of q, k, v and of the attention output (= d unless head_dim is set)
+  GemmArgs g{};
+  g.m = p->n_tokens;
+  switch (kernel_class) {
+    case TCMV_K_QKV_GEMM:
+      g.lda = g.k = d.d; g.n = 3 * da; g.epi = EPI_QKV;
+      g.ldc = bf ? 2 * da : 3 * d.d;
+      if (bf) {
+        g.split = 2 * da; g.qcols = da;
+        if (layer_attn(p, l).fused) { g.kn_dh = head_dim_of(d); g.kn_heads = d.heads; }
+      }
+      break;
+    case TCMV_K_OUT_GEMM:                          // accumulates into the residual stream; a norm follows
+      g.lda = g.k = da; g.ldc = g.n = d.d; g.epi = EPI_RESID; g.defer_reduce = 1;
+      break;
+    case TCMV_K_FC1_GEMM:                          // gated: (gate, up) column pairs -> one column of the output
+      g.lda = g.k = d.d; g.n = d.mlp_gated ? 2 * d.mlp : d.mlp; g.ldc = d.mlp; g.epi = d.mlp_gated ? EPI_GATED : EPI_GELU;
+      break;
+    case TCMV_K_FC2_GEMM:                          // likewise accumulates; behind the last layer a norm follows only if the model ends with one
+      g.lda = g.k = d.mlp; g.ldc = g.n = d.d; g.epi = EPI_RESID; g.defer_reduce = l + 1 < d.layers || d.final_ln;
+      break;
+    default: g.m = 0;
+  }
+  return g;
 }
 
 hipError_t run_gemm(const tcmv_ctx* ctx, const GemmArgs& g, hipStream_t s) {
@@ -655,6 +699,21 @@ int64_t tcmv_plan_row_map(const tcmv_plan* p, int which, const int32_t** out) {
   return (int64_t)v->size();
 }
 
+int tcmv_plan_key_norms(const tcmv_plan* p, int layer) {
+  if (!p || layer < 0 || layer >= p->ctx->desc.layers) return TCMV_E_INVALID_ARG;
+  const LayerAttn a = layer_attn(p, layer);
+  return a.fused ? 2 : a.key_norms ? 1 : 0;
+}
+
+const char* tcmv_plan_gemm_kernel(const tcmv_plan* p, int kernel_class, int layer) {
+  if (!p || p->ctx->desc.dtype != TCMV_BF16 || layer < 0 || layer >= p->ctx->desc.layers) return nullptr;
+  GemmArgs g = layer_product(p, kernel_class, layer);
+  if (g.m <= 0) return nullptr;
+  // only looked at for being there
+  if (g.epi == EPI_RESID && encode_ws(p).splitk_bytes) g.partial = reinterpret_cast<float*>(sizeof(float));
+  return gemm_bf16_kernel_name(g);
+}
+
 int tcmv_preprocess(tcmv_ctx* ctx, const tcmv_plan* p, const void* d_meta, void* d_patches, void* stream) {
   if (!ctx) return TCMV_E_INVALID_ARG;
   if (!p || p->ctx != ctx) return fail(ctx, TCMV_E_INVALID_ARG, "plan does not belong to this context");
@@ -749,49 +808,41 @@ int tcmv_encode(tcmv_ctx* ctx, const tcmv_plan* p, const void* d_meta, const voi
       return part ? launch_layernorm_slices(x, part, slices_bias, gm, bt, y, T, d.d, d.ln_eps, out_bf16, s, d.norm)
                   : launch_layernorm(x, gm, bt, y, T, d.d, d.ln_eps, out_bf16, s, d.norm); });
   };
-  // products that accumulate into x; `norm_follows`: the next kernel that touches x is a norm
-  auto accumulate = [&](GemmArgs& g, int cat, bool norm_follows) {
+  // products that accumulate into x
+  auto accumulate = [&](GemmArgs& g, int cat) {
     if (ws.splitk_bytes) {
       g.partial = reinterpret_cast<float*>(wsb + ws.splitk);
-      g.defer_reduce = norm_follows;
-      if (norm_follows && gemm_bf16_slices(g) > 1) { slices = g.partial; slices_bias = g.bias; }
+      if (g.defer_reduce && gemm_bf16_slices(g) > 1) { slices = g.partial; slices_bias = g.bias; }
     }
     return timed(ctx, cat, s, [&] { return run_gemm(ctx, g, s); });
   };
   for (int l = 0; l < d.layers; ++l) {
     const void* const* L = ctx->layer.data() + (size_t)l * 12;
     auto f = [&](int j) { return reinterpret_cast<const float*>(L[j]); };
-    const bool windowed = d.window && !(d.full_every && (l + 1) % d.full_every == 0);
+    const LayerAttn la = layer_attn(p, l);
+    const bool windowed = la.windowed;
     TCMV_CHECK(norm(f(0), f(1), xn, bf), "LN1");
-    bool use_kmax = false, kmax_fused = false;
     uint32_t *kmax = nullptr, *kmax_other = nullptr;
     const int32_t* row_seg = nullptr;
     {
-      GemmArgs g{};
-      g.a = xn; g.lda = d.d; g.w = L[2]; g.bias = f(3); g.m = T; g.n = 3 * da; g.k = d.d;
-      g.c = qkv; g.epi = EPI_QKV;
+      GemmArgs g = layer_product(p, TCMV_K_QKV_GEMM, l);
+      g.a = xn; g.w = L[2]; g.bias = f(3); g.c = qkv;
       if (bf) {
-        g.ldc = 2 * da; g.split = 2 * da; g.vt = vt; g.ldvt = p->ldvt();
+        g.vt = vt; g.ldvt = p->ldvt();
         g.vcol = dev<int32_t>(d_meta, windowed ? p->off_vcol_win : p->off_vcol);
         if (d.pos == TCMV_POS_ROTARY_2D) { g.rope = dev<float>(d_meta, p->off_rope); g.rope_dh = dh; }
         // the queries leave the projection already multiplied by softmax scale * log2(e)
-        g.qcols = da; g.qscale = (float)(1.4426950408889634 * attn_scale_of(d));
+        g.qscale = (float)(1.4426950408889634 * attn_scale_of(d));
         // largest key norm per (segment, head): lets the attention kernel drop the running maximum where the
         // scores are provably small.  The projection's epilogue computes it where its tiles line up with the heads.
-        const bool short_windows = windowed && p->max_win_len <= 64;
-        use_kmax = !short_windows && (windowed ? p->norm_bound_win : p->norm_bound);
-        if (use_kmax) {
+        if (la.key_norms) {
           kmax = reinterpret_cast<uint32_t*>(wsb + ws.kmax + (size_t)kblock * ws.kmax_bytes);
           kmax_other = reinterpret_cast<uint32_t*>(wsb + ws.kmax + (size_t)(kblock ^ 1) * ws.kmax_bytes);
           kblock ^= 1;
           row_seg = dev<int32_t>(d_meta, windowed ? p->off_row_seg_win : p->off_row_seg);
-          if (gemm_bf16_can_fuse_key_norms(T, 3 * da, d.d, da, dh)) {
-            g.kmax2 = kmax; g.row_seg = row_seg; g.kn_dh = dh; g.kn_heads = d.heads;
-            kmax_fused = true;
-          }
+          if (la.fused) { g.kmax2 = kmax; g.row_seg = row_seg; }
         }
       }
-      else { g.ldc = 3 * d.d; }
       TCMV_CHECK(timed(ctx, TCMV_K_QKV_GEMM, s, [&] { return run_gemm(ctx, g, s); }), "QKV GEMM");
     }
     {
@@ -804,17 +855,16 @@ int tcmv_encode(tcmv_ctx* ctx, const tcmv_plan* p, const void* d_meta, const voi
         const uint16_t* qk = reinterpret_cast<const uint16_t*>(qkv);
         a.q = qk; a.k = qk + da; a.ldqk = 2 * da; a.v = vt; a.ldv = p->ldvt();
         a.scale = 1.0f; a.prescaled = 1;
-        // windows of at most 64 tokens (8 x 8 patches): one small workgroup per window and head
-        const bool short_windows = windowed && p->max_win_len <= 64;
-        if (use_kmax) {
-          if (!kmax_fused)
+        if (la.key_norms) {
+          if (!la.fused)
             TCMV_CHECK(timed(ctx, TCMV_K_ATTENTION, s, [&] { return launch_knorm(qk + da, 2 * da, T, d.heads, dh, row_seg, kmax, s); }),
                        "key norms");
           a.kmax2 = kmax;
           a.any_left = kmax + (size_t)std::max(p->n_segments, p->n_windows) * d.heads * kKmaxStride;
           a.kmax_clear = kmax_other; a.n_clear = (int)(ws.kmax_bytes / 4);
         }
-        TCMV_CHECK(timed(ctx, TCMV_K_ATTENTION, s, [&] { return short_windows ? launch_attn_window_bf16(a, s) : launch_attn_bf16(a, s); }),
+        // windows of at most 64 tokens (8 x 8 patches): one small workgroup per window and head
+        TCMV_CHECK(timed(ctx, TCMV_K_ATTENTION, s, [&] { return la.short_windows ? launch_attn_window_bf16(a, s) : launch_attn_bf16(a, s); }),
                    "attention");
       } else {
         const float* q3 = reinterpret_cast<const float*>(qkv);
@@ -824,24 +874,20 @@ int tcmv_encode(tcmv_ctx* ctx, const tcmv_plan* p, const void* d_meta, const voi
       }
     }
     {
-      GemmArgs g{};
-      g.a = xn; g.lda = da; g.w = L[4]; g.bias = f(5); g.c = x; g.ldc = d.d; g.m = T; g.n = d.d; g.k = da;
-      g.epi = EPI_RESID;
-      TCMV_CHECK(accumulate(g, TCMV_K_OUT_GEMM, true), "out-proj GEMM");
+      GemmArgs g = layer_product(p, TCMV_K_OUT_GEMM, l);
+      g.a = xn; g.w = L[4]; g.bias = f(5); g.c = x;
+      TCMV_CHECK(accumulate(g, TCMV_K_OUT_GEMM), "out-proj GEMM");
     }
     TCMV_CHECK(norm(f(6), f(7), xn, bf), "LN2");
     {
-      GemmArgs g{};
-      g.a = xn; g.lda = d.d; g.w = L[8]; g.bias = f(9); g.c = hbuf; g.ldc = d.mlp; g.m = T; g.k = d.d;
-      if (d.mlp_gated) { g.n = 2 * d.mlp; g.epi = EPI_GATED; }      // (gate, up) column pairs -> one column of hbuf
-      else { g.n = d.mlp; g.epi = EPI_GELU; }
+      GemmArgs g = layer_product(p, TCMV_K_FC1_GEMM, l);
+      g.a = xn; g.w = L[8]; g.bias = f(9); g.c = hbuf;
       TCMV_CHECK(timed(ctx, TCMV_K_FC1_GEMM, s, [&] { return run_gemm(ctx, g, s); }), "fc1 GEMM");
     }
     {
-      GemmArgs g{};
-      g.a = hbuf; g.lda = d.mlp; g.w = L[10]; g.bias = f(11); g.c = x; g.ldc = d.d; g.m = T; g.n = d.d; g.k = d.mlp;
-      g.epi = EPI_RESID;
-      TCMV_CHECK(accumulate(g, TCMV_K_FC2_GEMM, l + 1 < d.layers || d.final_ln), "fc2 GEMM");
+      GemmArgs g = layer_product(p, TCMV_K_FC2_GEMM, l);
+      g.a = hbuf; g.w = L[10]; g.bias = f(11); g.c = x;
+      TCMV_CHECK(accumulate(g, TCMV_K_FC2_GEMM), "fc2 GEMM");
     }
   }
   if (d.final_ln)
@@ -923,6 +969,14 @@ int tcmv_op_gemm(int dtype, int epilogue, const void* d_a, const void* d_w, cons
   g.epi = epilogue;
   const hipError_t e = dtype == TCMV_BF16 ? launch_gemm_bf16(g, (hipStream_t)stream) : launch_gemm_f32(g, (hipStream_t)stream);
   return e == hipSuccess ? TCMV_OK : TCMV_E_HIP;
+}
+
+const char* tcmv_op_gemm_kernel(int epilogue, int64_t m, int n, int k) {
+  const bool gated = epilogue == EPI_GATED;
+  if (epilogue < 0 || (epilogue > 2 && !gated) || m <= 0 || n <= 0 || k <= 0) return nullptr;
+  GemmArgs g{};
+  g.lda = k; g.ldc = gated ? n / 2 : n; g.m = m; g.n = n; g.k = k; g.epi = epilogue;
+  return gemm_bf16_kernel_name(g);
 }
 
 namespace {

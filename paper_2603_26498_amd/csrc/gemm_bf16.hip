@@ -972,6 +972,13 @@ bool gemm_bf16_can_fuse_key_norms(int64_t m, int n, int k, int qcols, int dh) {
   return gk != GK_INVALID && wave_tile_holds_heads(tn, qcols, dh) && (!is_persistent(gk) || n % bn == 0);
 }
 
+const char* gemm_bf16_kernel_name(const GemmArgs& a) {
+  static const char* const names[] = {nullptr, "256x320 persistent", "256x256 persistent", "192x256", "256x160", "256x128", "128x160",
+                                      "128x128 k/2", "128x128", "64x64", "128x128 slices", "64x64 slices"};   // GemmKernel order
+  int tn = 0, bn = 0;
+  return names[choose_kernel(a, &tn, &bn)];
+}
+
 int gemm_bf16_slices(const GemmArgs& a) {
   int tn = 0, bn = 0;
   const GemmKernel gk = choose_kernel(a, &tn, &bn);

@@ -132,6 +132,7 @@ hipError_t launch_layernorm_slices(float* x, const float* partial, const float* 
                                    int64_t rows, int d, float eps, int out_bf16, hipStream_t s, int rms);
 hipError_t launch_stream_ref(const void* in, size_t in_bytes, void* out, size_t out_bytes, hipStream_t s);
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s);
+const char* gemm_bf16_kernel_name(const GemmArgs& a);   // of the kernel that launch_gemm_bf16 takes; null: it refuses
 int gemm_bf16_slices(const GemmArgs& a);   // slices of k that launch_gemm_bf16 computes separately (1 or 4)
 // true when launch_gemm_bf16 computes the key-norm maxima in the epilogue of an m x n x k QKV projection whose key
 // columns are [qcols, 2 qcols) with heads of dh columns (the wave tiles must line up with the heads)

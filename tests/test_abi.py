@@ -230,3 +230,21 @@ def test_windowed_plan_whose_transposed_values_do_not_fit_32_bit_offsets_is_refu
 def test_rows_of_an_attention_work_item(heads, dh, lens, rows):
     cu = [0] + [int(c) for c in np.cumsum(lens)]
     assert B.tcmv_op_attention_rows(B.TCMV_BF16, cu, heads * dh, heads) == rows
+
+
+def _host_plan(desc, sizes):
+    """Plan of still images given in patches (no weights, nothing uploaded) and the encoder that owns it."""
+    p = desc.patch
+    return _plan(desc, [workloads.Item(workloads.IMAGE, 1, h * p, w * p, h * p, w * p, None) for h, w in sizes])
+
+
+def test_route_queries_answer_on_the_host():
+    enc, pl = _host_plan(workloads.qwen_like_desc(), [(16, 16)])
+    names = {c: B.tcmv_plan_gemm_kernel(pl.handle, c, 0) for c in ("qkv_gemm", "out_gemm", "fc1_gemm", "fc2_gemm")}
+    assert names["qkv_gemm"] == names["fc1_gemm"] == "64x64" and names["out_gemm"] == names["fc2_gemm"] == "64x64 slices"
+    assert B.tcmv_plan_gemm_kernel(pl.handle, "layernorm", 0) is None and B.tcmv_plan_gemm_kernel(pl.handle, "qkv_gemm", 32) is None
+    assert B.tcmv_plan_key_norms(pl.handle, 0) == 0 and B.tcmv_plan_key_norms(pl.handle, -1) < 0
+    assert B.tcmv_op_gemm_kernel(B.EPI_STORE, 32768, 3840, 1280) == "256x320 persistent"
+    assert B.tcmv_op_gemm_kernel(B.EPI_STORE, 100, 100, 100) is None       # k must be a multiple of 64
+    enc, pl = _host_plan(workloads.small_config(1).desc, [(14, 14)])       # fp32: no bf16 kernel
+    assert B.tcmv_plan_gemm_kernel(pl.handle, "qkv_gemm", 0) is None and B.tcmv_plan_key_norms(pl.handle, 0) == 0
