@@ -874,23 +874,29 @@ static hipError_t launch_persist(const GemmArgs& a, hipStream_t s) {
 namespace {
 enum GemmKernel { GK_INVALID, GK_P320, GK_P256, GK_T192x256, GK_T256x160, GK_T256x128, GK_T128x160, GK_T128K2, GK_T128, GK_T64, GK_SPLIT128, GK_SPLIT64 };
 
-// Tile kernels and what one workgroup's tile costs: `base` microseconds (launch, first loads, write-out) plus `per_k` for
-// every 64 elements of k.  Those with shared = 0 fill a CU's LDS (rounds of 256 tiles); of the shared ones two (T128)
-// or three (T64) run on a CU, where the cost of a k-tile grows with the tiles per CU from a floor, the memory latency.
-// Fitted to measurements at 256 .. 18432 rows, n 1024 .. 6912, k 1024 .. 5120; of 39 such products the choice is within
-// 3 % of the best kernel on 35, within 10 % on the others.
-struct TileKernel { GemmKernel kernel; int bm, bn, wave_n, shared; float base, per_k, floor_k; };
+// Tile kernels and what one workgroup's tile costs: `base` microseconds (first loads, write-out) plus `per_k` for every 64
+// elements of k.  Those with shared = 0 fill a CU's LDS: they run in rounds of 256 tiles, and each round after the first
+// costs `more` on top.  Of the shared ones two (T128) or three (T64) run on a CU; the cost of a k-tile grows with the tiles
+// per CU from a floor, the memory latency (`more`).  Products that accumulate read and write four bytes per element:
+// 12.6 us for a 256x256 tile on a CU of its own (all CUs write out together), 0.9 where other tiles compute meanwhile.
+// Fitted to 933 products of fewer than 400 tiles of 256x256: every layer product of five encoders at 64 .. 23184 rows,
+// measured inside passes over 12 layers, whose weights come from memory (they exceed the last-level cache), and single
+// products with k from 128 to 8192 over weights that do too.  The kernel with the lowest estimate is on average 0.5 % slower
+// than the fastest (more than 5 % on 31 products, more than 10 % on 6); the estimates themselves are off by 15 % r.m.s.
+struct TileKernel { GemmKernel kernel; int bm, bn, wave_n, shared; float base, per_k, more; };
 constexpr TileKernel kTileKernels[] = {
-    {GK_P256, 256, 256, 64, 0, 5.0f, 1.65f, 0.f},      {GK_P320, 256, 320, 160, 0, 8.0f, 1.75f, 0.f},
-    {GK_T192x256, 192, 256, 128, 0, 16.f, 1.35f, 0.f}, {GK_T256x160, 256, 160, 160, 0, 9.0f, 1.05f, 0.f},
-    {GK_T256x128, 256, 128, 64, 0, 7.5f, 0.85f, 0.f},  {GK_T128x160, 128, 160, 160, 0, 5.0f, 0.70f, 0.f},
-    {GK_T128K2, 128, 128, 64, 0, 3.5f, 0.53f, 0.f},    {GK_T128, 128, 128, 64, 1, 6.0f, 0.55f, 0.80f},
-    {GK_T64, 64, 64, 32, 1, 2.0f, 0.22f, 0.36f}};
+    {GK_P320, 256, 320, 160, 0, 6.9f, 1.75f, 0.f},      {GK_P256, 256, 256, 64, 0, 3.5f, 1.51f, 4.4f},
+    {GK_T192x256, 192, 256, 128, 0, 9.3f, 1.30f, 0.2f}, {GK_T256x160, 256, 160, 160, 0, 5.1f, 1.05f, 2.8f},
+    {GK_T256x128, 256, 128, 64, 0, 4.2f, 0.79f, 5.5f},  {GK_T128x160, 128, 160, 160, 0, 9.0f, 0.57f, 0.f},
+    {GK_T128K2, 128, 128, 64, 0, 4.7f, 0.44f, 1.0f},    {GK_T128, 128, 128, 64, 1, 3.1f, 0.55f, 0.81f},
+    {GK_T64, 64, 64, 32, 1, 3.2f, 0.22f, 0.35f}};
 
-float tile_cost(const TileKernel& t, int64_t m, int n, int k, int slices) {
+float tile_cost(const TileKernel& t, int64_t m, int n, int k, int slices, bool accumulates) {
   const int64_t tiles = ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn) * slices;
   const float per_cu = (float)((tiles + 255) / 256), nk = (float)(k / 64 / slices);
-  return t.shared ? t.base + nk * std::max(t.floor_k, t.per_k * per_cu) : per_cu * (t.base + nk * t.per_k);
+  const float out = accumulates ? (t.shared ? 0.9f : 12.6f) * (float)(t.bm * t.bn) / 65536.f : 0.f;
+  return t.shared ? t.base + nk * std::max(t.more, t.per_k * per_cu) + per_cu * out
+                  : per_cu * (t.base + nk * t.per_k + out) + (per_cu - 1.f) * t.more;
 }
 
 // a wave tile of `wave_n` columns computes key norms: whole heads, at most four, starting at head boundaries
@@ -931,29 +937,32 @@ GemmKernel choose_kernel(const GemmArgs& a, int* wave_tile_n, int* block_n) {
   }
   // Smaller products: a few rounds of tiles at most, so the round that is only partly filled decides.  The kernel with
   // the lowest estimate is taken (4096 x 1280 x 5120: 63 us with 128x160 tiles, 79 with 128x128; 4096 x 5120 x 1280:
-  // 54 with one round of 256x320 tiles, 79 with 128x128; 256 x 5120 x 1280: 14 with 64x64, 20 - 27 with larger tiles).
-  // Where key norms are wanted (kn_dh), a tile that cannot compute them pays for the separate pass over the keys
-  // (13 us at 4096 rows, 21 at 25772).
+  // 54 with one round of 256x320 tiles, 75 with 128x128; 256 x 5120 x 1280: 16 with 64x64, 19 - 45 with larger tiles).
+  // Where key norms are wanted (kn_dh), a tile that cannot compute them pays for the separate pass over the keys (12 - 20
+  // us), one that can for the sums in its write-out (1 - 14 us; they grow with the rows and more with the smaller tiles).
   const TileKernel* best = nullptr;
   float best_cost = 0.f;
   for (const TileKernel& t : kTileKernels) {
     if (is_persistent(t.kernel) && !can_persist) continue;
-    float c = tile_cost(t, a.m, a.n, a.k, 1);
-    if (a.epi == EPI_QKV && a.kn_dh &&
-        !(wave_tile_holds_heads(t.wave_n, a.qcols, a.kn_dh) && (!is_persistent(t.kernel) || a.n % t.bn == 0)))
-      c += 11.5f + 4e-4f * (float)a.m;
+    float c = tile_cost(t, a.m, a.n, a.k, 1, a.epi == EPI_RESID);
+    if (a.epi == EPI_QKV && a.kn_dh) {
+      if (!wave_tile_holds_heads(t.wave_n, a.qcols, a.kn_dh) || (is_persistent(t.kernel) && a.n % t.bn)) c += 13.f + 2e-4f * (float)a.m;
+      else c += is_persistent(t.kernel) ? 3.f + 2e-4f * (float)a.m : 1.f + 5e-4f * (float)a.m;
+    }
     if (!best || c < best_cost) { best = &t; best_cost = c; }
   }
   *wave_tile_n = best->wave_n; *block_n = best->bn;
   // A contraction over few rows that accumulates (out-projection and fc2 of one small request): a quarter of k per
   // workgroup, added to C in a fixed order by a second kernel or by the norm that follows (defer_reduce), where that is
-  // estimated to win in spite of it (256 x 1280 x 5120: 12.5 us + 3.9 with 64x64 tiles, 30 unsplit; 1120 rows: 28 + 6.4
-  // with 128x128 tiles, 37 unsplit; 256 x 1280 x 1280: 5.8 against 7.9, 560 rows 8.7 against 8.3).
+  // estimated to win in spite of it.  What it costs, the slices written and read again, grows with the output: measured
+  // with the longer norm, 256 x 1280 x 1280 7 us against 10 unsplit, 576 rows 9.5 / 9.7; 256 x 1280 x 5120 14 / 30, 1024
+  // rows 30 (128x128 tiles) / 42, 1440 rows 33 / 41, 1760 rows 48 / 48.
   if (a.epi == EPI_RESID && a.partial && a.k >= (a.defer_reduce ? 1024 : 2048) && (a.k / 64) % 4 == 0) {
     GemmKernel split = GK_INVALID;
+    const float elements = 1e-6f * (float)a.m * (float)a.n;
     for (const TileKernel& t : kTileKernels) {
       if (!t.shared) continue;
-      const float c = tile_cost(t, a.m, a.n, a.k, 4) + (a.defer_reduce ? 2.5f : 5.4f) + 1.75e-6f * (float)a.m * (float)a.n;
+      const float c = tile_cost(t, a.m, a.n, a.k, 4, false) + (a.defer_reduce ? 0.75f : 3.65f) + (t.kernel == GK_T64 ? 4.f : 3.5f) * elements;
       if (c < best_cost) { best_cost = c; split = t.kernel == GK_T64 ? GK_SPLIT64 : GK_SPLIT128; }
     }
     if (split != GK_INVALID) return split;

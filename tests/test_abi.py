@@ -248,3 +248,28 @@ def test_route_queries_answer_on_the_host():
     assert B.tcmv_op_gemm_kernel(B.EPI_STORE, 100, 100, 100) is None       # k must be a multiple of 64
     enc, pl = _host_plan(workloads.small_config(1).desc, [(14, 14)])       # fp32: no bf16 kernel
     assert B.tcmv_plan_gemm_kernel(pl.handle, "qkv_gemm", 0) is None and B.tcmv_plan_key_norms(pl.handle, 0) == 0
+
+
+# products on which an earlier estimate took a kernel 8 - 40 % slower than the one named (weights read from memory)
+@pytest.mark.parametrize("epi,m,n,k,kernel", [
+    (B.EPI_STORE, 8192, 3072, 128, "128x128"), (B.EPI_STORE, 4096, 3072, 128, "128x128"), (B.EPI_STORE, 12288, 1024, 128, "128x128"),
+    (B.EPI_STORE, 1024, 3072, 512, "128x128 k/2"), (B.EPI_STORE, 8192, 1024, 256, "256x128"), (B.EPI_STORE, 2048, 3072, 512, "256x128"),
+    (B.EPI_GATED, 576, 8192, 1024, "256x128"), (B.EPI_GATED, 640, 8192, 1024, "256x128"), (B.EPI_GELU, 1280, 4096, 1024, "256x128"),
+    (B.EPI_RESID, 8192, 1024, 128, "128x128"), (B.EPI_RESID, 10240, 1024, 1024, "128x128"), (B.EPI_RESID, 11520, 1024, 1024, "128x128"),
+    (B.EPI_RESID, 8464, 1280, 1280, "128x128"), (B.EPI_RESID, 9216, 1152, 1280, "128x128"), (B.EPI_RESID, 2304, 1280, 1280, "64x64"),
+    (B.EPI_RESID, 2688, 1024, 1024, "64x64"), (B.EPI_RESID, 10240, 1152, 4352, "128x128 k/2")])
+def test_kernels_of_products_that_an_estimate_got_wrong(epi, m, n, k, kernel):
+    assert B.tcmv_op_gemm_kernel(epi, m, n, k) == kernel
+
+
+# side of one still image in patches -> kernels of the two products that accumulate (1280 wide, mlp 5120): slices of k where
+# they pay together with the norm that adds them, in the tiles that are faster (896 rows: 31 us a layer with 128x128 tiles, 37
+# with 64x64; 1760 rows: 51 unsplit, 51 in slices)
+@pytest.mark.parametrize("side,out,fc2", [
+    ((16, 16), "64x64 slices", "64x64 slices"), ((20, 24), "64x64 slices", "64x64 slices"), ((24, 32), "64x64", "128x128 slices"),
+    ((28, 32), "64x64", "128x128 slices"), ((32, 32), "64x64", "128x128 slices"), ((36, 40), "64x64", "128x128 slices"),
+    ((44, 48), "64x64", "128x128 k/2")])
+def test_where_products_are_cut_along_k(side, out, fc2):
+    enc, pl = _host_plan(workloads.qwen_like_desc(), [side])
+    assert B.tcmv_plan_gemm_kernel(pl.handle, "out_gemm", 0) == out
+    assert B.tcmv_plan_gemm_kernel(pl.handle, "fc2_gemm", 0) == fc2

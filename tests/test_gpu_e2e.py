@@ -276,7 +276,7 @@ def test_single_small_request_with_long_mlp_contraction():
 def test_products_cut_along_k_and_added_by_the_norm(h, w, rms, final_ln):
     """One small image through full-width layers: the products that accumulate are computed in four slices of k, which
     the following norm (or, behind the last layer, a kernel of its own) adds to the residual stream; 256, 252 and 1080
-    tokens, LayerNorm and RMSNorm, with and without a final norm."""
+    tokens (fc2 only), LayerNorm and RMSNorm, with and without a final norm."""
     import dataclasses
     if rms:
         desc = dataclasses.replace(workloads.windowed_desc(layers=2, d=1280, heads=16, mlp=5120, out_dim=0, window=8, full_every=2), merge=2)
@@ -289,5 +289,7 @@ def test_products_cut_along_k_and_added_by_the_norm(h, w, rms, final_ln):
     for key, x in wl.weights.items():
         wl.weights[key] = workloads.snap_to_bf16_grid(x)
     ref = oracle.run(wl)
-    _, _, _, hidden, _ = run_gpu(wl)
+    _, pl, _, hidden, _ = run_gpu(wl)
+    routes = [B.tcmv_plan_gemm_kernel(pl.handle, c, 0) for c in ("out_gemm", "fc2_gemm")]
+    assert routes == (["64x64", "128x128 slices"] if h == 420 else ["64x64 slices"] * 2)
     assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, "hidden")

@@ -64,7 +64,6 @@ def _gemm_ref(a, w, bias, epi, c0):
 
 @pytest.mark.parametrize("m,n,k", [(1, 64, 64), (127, 128, 64), (128, 128, 128), (300, 320, 640), (1000, 1280, 1216),
                                    (257, 136, 192), (129, 3840, 1280), (2050, 1280, 5120),
-                                   # 200..511 tiles of 128x128: the mid-size tile kernel (smaller ones use 64x64 tiles)
                                    (2050, 1928, 320), (1500, 2560, 128), (3333, 1280, 192)])
 @pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_GELU, B.EPI_RESID])
 def test_gemm_bf16(m, n, k, epi):
@@ -491,13 +490,26 @@ def test_attention_f32_infinities_stay_where_they_belong(dh):
     assert np.abs(got[ok] - ref[ok]).max() <= 2e-5 * max(1.0, np.abs(ref[ok]).max())
 
 
-# ragged in both directions; in this order the tiles are 64x64, 128x128 (k shared by two waves), 128x160, 256x128, 256x160,
-# 192x256, 256x256, 256x320, 128x128, with the shortest contractions that each of them is taken for
-@pytest.mark.parametrize("m,n,k", [(239, 816, 64), (837, 3504, 256), (4560, 1096, 320), (6769, 1032, 448), (8671, 1032, 448),
-                                   (8210, 1128, 768), (8490, 1672, 128), (7711, 2248, 192), (8393, 2312, 192)])
-@pytest.mark.parametrize("epi", [B.EPI_STORE, B.EPI_RESID])
-def test_gemm_bf16_tile_kernels(m, n, k, epi):
-    test_gemm_bf16(m, n, k, epi)
+# one product for every tile kernel and epilogue, ragged in both directions, with short contractions (fewer k-tiles than
+# stages where the kernel is taken for them)
+TILE_KERNEL_CASES = [
+    (B.EPI_STORE, 37, 136, 64, "64x64"), (B.EPI_STORE, 12747, 200, 64, "128x128"), (B.EPI_STORE, 10881, 136, 512, "128x128 k/2"),
+    (B.EPI_STORE, 11047, 280, 1536, "128x160"), (B.EPI_STORE, 1349, 6832, 2048, "192x256"), (B.EPI_STORE, 13927, 272, 256, "256x128"),
+    (B.EPI_STORE, 13379, 568, 256, "256x160"), (B.EPI_STORE, 13091, 520, 192, "256x256 persistent"), (B.EPI_STORE, 2827, 5656, 256, "256x320 persistent"),
+    (B.EPI_GELU, 9803, 272, 64, "128x128"), (B.EPI_GELU, 12331, 136, 448, "128x128 k/2"), (B.EPI_GELU, 11037, 280, 1536, "128x160"),
+    (B.EPI_GELU, 10977, 840, 2048, "192x256"), (B.EPI_GELU, 9347, 392, 256, "256x128"), (B.EPI_GELU, 1153, 6584, 256, "256x160"),
+    (B.EPI_RESID, 33, 144, 64, "64x64"), (B.EPI_RESID, 10475, 264, 64, "128x128"), (B.EPI_RESID, 10969, 152, 1536, "128x128 k/2"),
+    (B.EPI_RESID, 13393, 264, 1280, "128x160"), (B.EPI_RESID, 1685, 7064, 1536, "192x256"), (B.EPI_RESID, 12287, 336, 1536, "256x128"),
+    (B.EPI_RESID, 7455, 1032, 1024, "256x160"), (B.EPI_RESID, 6181, 3944, 128, "256x256 persistent"), (B.EPI_RESID, 14463, 2144, 128, "256x320 persistent"),
+    (B.EPI_GATED, 33, 144, 64, "64x64"), (B.EPI_GATED, 12667, 208, 64, "128x128"), (B.EPI_GATED, 11251, 144, 448, "128x128 k/2"),
+    (B.EPI_GATED, 11051, 272, 1536, "128x160"), (B.EPI_GATED, 13325, 656, 2048, "192x256"), (B.EPI_GATED, 13813, 272, 256, "256x128"),
+    (B.EPI_GATED, 13279, 528, 256, "256x160"), (B.EPI_GATED, 9441, 800, 192, "256x256 persistent"), (B.EPI_GATED, 12563, 1552, 192, "256x320 persistent")]
+
+
+@pytest.mark.parametrize("epi,m,n,k,kernel", TILE_KERNEL_CASES)
+def test_gemm_bf16_tile_kernels(epi, m, n, k, kernel):
+    assert B.tcmv_op_gemm_kernel(epi, m, n, k) == kernel
+    (test_gated_epilogue if epi == B.EPI_GATED else test_gemm_bf16)(*((m, n, k) if epi == B.EPI_GATED else (m, n, k, epi)))
 
 
 @pytest.mark.parametrize("lens,qs,big_head", [([4096, 2048, 2048], 6.0, None), ([4096, 4096], 1.0, 3)])
