@@ -571,10 +571,22 @@ int tcmv_plan_create(tcmv_ctx* ctx, const tcmv_item* items, int n_items, tcmv_pl
     for (int64_t n : len) { rows += (double)n; pairs += (double)n * (double)n; }
     return rows > 0 && pairs >= 1024.0 * rows;
   };
-  // A small request (128-row items that do not give every CU two workgroups) waits for memory and barriers rather than for
-  // the vector unit: the reference-free loop saves 0.7 us at 1120 tokens (23.8 against 24.5) and the second launch costs 4.6.
+  // A small request (128-row items that do not give every CU two workgroups) waits for memory and barriers more than for
+  // the vector unit: the reference-free loop then saves 0.1 us for every 64 keys where an item has a CU to itself and 0.28
+  // where two share one, against 4.6 us for the second launch and the key norms (nearly free in the QKV product for heads
+  // of 64; a worse tile or a pass of 7 us for heads of 80, a pass for the others).  Measured over 332 such requests, whole
+  // layers, this rule loses at most 2 % against the better choice: 4 heads of 32, 14400 keys 280 us without, 227 with; 16 of 64,
+  // 2112 keys 151 / 147, 1280 keys 107 / 110; 16 of 80, 1152 keys 127 / 128; 4 of 96, 14400 keys 487 / 434, 4096 keys 134 / 138.
+  auto small_request_pays = [&]() {
+    double rows = 0, pairs = 0;
+    for (int64_t n : seg_len) { rows += (double)n; pairs += (double)n * (double)n; }
+    const int dh = head_dim_of(d);
+    const double items = (double)p->work.size() * d.heads;
+    const double cost = dh == 64 ? 5.0 : dh == 80 ? 12.0 : 6.0 + 0.008 * (double)attn_width_of(d);
+    return pairs / 64.0 * (items > 256 ? 0.28 : 0.1) >= cost * rows;
+  };
   const bool small_request = p->bq == 128 && (int64_t)p->work.size() * d.heads < 512;
-  p->norm_bound = d.dtype == TCMV_BF16 && !small_request && long_enough(seg_len);
+  p->norm_bound = d.dtype == TCMV_BF16 && long_enough(seg_len) && (!small_request || small_request_pays());
   p->norm_bound_win = d.dtype == TCMV_BF16 && long_enough(win_len);
   p->n_windows = (int)win_start.size();
   for (int64_t n : win_len) p->max_win_len = std::max(p->max_win_len, n);

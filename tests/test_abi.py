@@ -273,3 +273,19 @@ def test_where_products_are_cut_along_k(side, out, fc2):
     enc, pl = _host_plan(workloads.qwen_like_desc(), [side])
     assert B.tcmv_plan_gemm_kernel(pl.handle, "out_gemm", 0) == out
     assert B.tcmv_plan_gemm_kernel(pl.handle, "fc2_gemm", 0) == fc2
+
+
+# whether the reference-free attention pass and the key norms it needs pay for one image (sides in patches): with few heads
+# or long segments they do although the work items are few, where they were measured to (and short ones do without)
+@pytest.mark.parametrize("heads,dh,side,n,pays", [
+    (4, 32, (120, 120), 1, True), (4, 64, (120, 120), 1, True), (4, 96, (120, 120), 1, True), (4, 80, (120, 120), 1, True),
+    (8, 64, (84, 92), 1, True), (8, 96, (84, 92), 1, True), (8, 80, (84, 92), 1, True), (2, 64, (84, 92), 1, True),
+    (16, 64, (44, 48), 1, True), (16, 64, (56, 56), 1, True), (12, 64, (64, 64), 1, True), (8, 64, (40, 64), 2, True),
+    (16, 80, (32, 36), 1, False), (16, 80, (40, 44), 1, False), (16, 64, (32, 40), 1, False), (4, 96, (64, 64), 1, False),
+    (8, 96, (32, 40), 4, False), (2, 32, (48, 48), 1, False), (16, 80, (64, 68), 1, True), (16, 96, (64, 72), 1, True)])
+def test_where_key_norms_pay(heads, dh, side, n, pays):
+    desc = workloads.ModelDesc(layers=1, d=heads * dh, heads=heads, mlp=256, patch=14, tpatch=1, merge=1)
+    enc, pl = _host_plan(desc, [side] * n)
+    norms = B.tcmv_plan_key_norms(pl.handle, 0)
+    assert (norms > 0) == pays
+    assert norms < 2 or dh in (64, 80)          # only whole heads of these sizes fit the write-out of the QKV product

@@ -213,18 +213,40 @@ def test_per_request_pipeline_matches_plan_by_plan_runs():
 
 @pytest.mark.parametrize("std", [0.02, 0.08])
 def test_long_segments_take_the_norm_bounded_attention_path(std):
-    """Segments of 4096 and 2304 tokens make the library compute key norms and run attention without a softmax
+    """Segments of 8192 and 2304 tokens make the library compute key norms and run attention without a softmax
     reference where the bound allows it; the result must not depend on which copy of the kernel ran."""
     desc = workloads.qwen_like_desc(layers=2, d=320, heads=4, mlp=640, out_dim=192, max_grid=48)
     rng = np.random.default_rng(9)
-    items = [workloads.Item(2, 8, 448, 448, 448, 448, workloads.random_frames(rng, 8, 448, 448)),
+    items = [workloads.Item(2, 16, 448, 448, 448, 448, workloads.random_frames(rng, 16, 448, 448)),
              workloads.Item(1, 1, 672, 672, 672, 672, workloads.random_frames(rng, 1, 672, 672))]
     wl = workloads.Workload("long", desc, items, workloads.make_weights(desc, 31, std=std, random_affine=True))
     ref = oracle.run(wl, workers=4)
     enc, pl, patches, hidden, out = run_gpu(wl)
-    assert pl.cu_seqlens == [0, 4096, 4096 + 2304]
+    assert pl.cu_seqlens == [0, 8192, 8192 + 2304]
+    assert B.tcmv_plan_key_norms(pl.handle, 0) > 0
     assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, "long segments hidden")
     assert_tokens_close(out.float().cpu().numpy(), ref["out"], 2e-2, 0.999, "long segments out")
+
+
+@pytest.mark.parametrize("heads,dh,side,n,kernel", [
+    (2, 64, (57, 57), 1, "128x128"), (6, 64, (37, 87), 1, "128x128 k/2"), (18, 64, (36, 33), 2, "192x256"), (4, 64, (35, 38), 6, "256x128"),
+    (8, 64, (39, 36), 4, "256x256 persistent"), (4, 80, (45, 61), 3, "256x160"), (4, 80, (81, 34), 4, "256x320 persistent")])
+@pytest.mark.parametrize("spread", [0.36, 1.43])
+def test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(heads, dh, side, n, kernel, spread):
+    """Two layers with rotary positions, RMSNorm and gated MLP, ragged rows: the QKV product squares and sums the keys on
+    their way out, into alternating tables that the attention of the layer before clears.  Weights of standard deviation
+    spread / sqrt(d) give queries and keys of standard deviation `spread` at every width, scores of spread^2 (bounded by
+    the norms, or not).  Queries and keys are rounded to bf16 (2^-9 of each), which moves a score by about 2^-8 of itself and
+    its probability by as much: 1 % for scores near 2, inside the bar; scores of 7 (spread 2.7) would miss it."""
+    desc = workloads.ModelDesc(layers=2, d=heads * dh, heads=heads, mlp=128, patch=14, tpatch=1, merge=1, pos="rope2d", norm="rms", gated=1)
+    rng = np.random.default_rng(heads + dh)
+    items = [workloads.Item(workloads.IMAGE, 1, 14 * side[0], 14 * side[1], 14 * side[0], 14 * side[1],
+                            workloads.random_frames(rng, 1, 14 * side[0], 14 * side[1])) for _ in range(n)]
+    wl = workloads.Workload("key_norms", desc, items, workloads.make_weights(desc, 32, std=spread / desc.d ** 0.5, random_affine=True))
+    ref = oracle.run(wl, workers=4)
+    enc, pl, patches, hidden, out = run_gpu(wl)
+    assert B.tcmv_plan_key_norms(pl.handle, 0) == 2 and B.tcmv_plan_gemm_kernel(pl.handle, "qkv_gemm", 0) == kernel
+    assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, kernel)
 
 
 @pytest.mark.parametrize("dh", [80, 64])
