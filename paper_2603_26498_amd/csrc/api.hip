@@ -276,6 +276,8 @@ LayerAttn layer_attn(const tcmv_plan* p, int l) {
   a.short_windows = a.windowed && p->max_win_len <= 64;
   a.key_norms = d.dtype == TCMV_BF16 && !a.short_windows && (a.windowed ? p->norm_bound_win : p->norm_bound);
   a.fused = a.key_norms && gemm_bf16_can_fuse_key_norms(p->n_tokens, 3 * attn_width_of(d), d.d, attn_width_of(d), head_dim_of(d));
+  // an attention too wide for the pass over the keys (more than 56 heads of 64) goes without, unless the product computes them
+  a.key_norms = a.fused || (a.key_norms && knorm_available(d.heads, head_dim_of(d)));
   return a;
 }
 

@@ -727,15 +727,17 @@ __global__ __launch_bounds__(256) void knorm_kernel(const uint16_t* k, int64_t l
   }
 }
 
+// LDS of the pass: chunk sums and norms of 32 rows
+static size_t knorm_lds(int heads, int dh) { return (size_t)32 * heads * (dh / 8 + 1) * sizeof(float); }
+
+bool knorm_available(int heads, int dh) { return dh % 8 == 0 && heads > 0 && heads <= 256 && knorm_lds(heads, dh) <= 64 * 1024; }
+
 hipError_t launch_knorm(const void* k, int64_t ldk, int64_t rows, int heads, int dh, const int32_t* row_seg,
                         uint32_t* kmax2, hipStream_t s) {
   if (rows == 0) return hipSuccess;
-  if (dh % 8 || heads <= 0 || heads > 256 || ldk % 8) return hipErrorInvalidValue;
-  const int cph = dh / 8;
-  const size_t lds = (size_t)32 * heads * (cph + 1) * sizeof(float);
-  if (lds > 64 * 1024) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(knorm_kernel, dim3((unsigned)((rows + 31) / 32)), dim3(256), lds, s,
-                     reinterpret_cast<const uint16_t*>(k), ldk, rows, heads, cph, row_seg, kmax2);
+  if (!knorm_available(heads, dh) || ldk % 8) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(knorm_kernel, dim3((unsigned)((rows + 31) / 32)), dim3(256), knorm_lds(heads, dh), s,
+                     reinterpret_cast<const uint16_t*>(k), ldk, rows, heads, dh / 8, row_seg, kmax2);
   return hipGetLastError();
 }
 

@@ -147,6 +147,7 @@ hipError_t launch_transpose_v(const void* v, int64_t ldv, const int32_t* vcol, v
                               int64_t rows, int d, hipStream_t s);
 // kmax2[row_seg[r]][h] = max(kmax2[..], |k[r, h*dh .. (h+1)*dh)|^2) over all rows (bf16 keys, row stride ldk elements);
 // kmax2 holds float bits and must be zero-filled before the call
+bool knorm_available(int heads, int dh);   // launch_knorm takes this many heads (its sums fit LDS)
 hipError_t launch_knorm(const void* k, int64_t ldk, int64_t rows, int heads, int dh, const int32_t* row_seg,
                         uint32_t* kmax2, hipStream_t s);
 // zero fill of a 16-byte aligned region whose size is a multiple of 16

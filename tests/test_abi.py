@@ -289,3 +289,16 @@ def test_where_key_norms_pay(heads, dh, side, n, pays):
     norms = B.tcmv_plan_key_norms(pl.handle, 0)
     assert (norms > 0) == pays
     assert norms < 2 or dh in (64, 80)          # only whole heads of these sizes fit the write-out of the QKV product
+
+
+@pytest.mark.parametrize("heads,dh,side,norms", [(60, 64, 39, 0), (64, 64, 36, 0), (84, 64, 33, 0), (56, 64, 39, None), (60, 96, 66, 0), (28, 80, 99, None)])
+def test_attention_too_wide_for_the_pass_over_the_keys_goes_without_norms(heads, dh, side, norms):
+    """The separate pass holds at most 512 chunk sums and norms of a row: wider models keep running, without the norms
+    (or with those of the QKV product)."""
+    ctx = B.tcmv_create(B.make_desc(dtype="bf16", layers=1, d=1024, heads=heads, mlp=256, patch=14, tpatch=1, merge=1, head_dim=dh, attn_scale=0.1))
+    plan = B.tcmv_plan_create(ctx, [(workloads.IMAGE, 1, side * 14, side * 14, side * 14, side * 14, None)])
+    got = B.tcmv_plan_key_norms(plan, 0)
+    B.tcmv_plan_destroy(plan)
+    B.tcmv_destroy(ctx)
+    assert got == norms if norms is not None else got > 0
+    assert got != 1 or heads * (dh // 8 + 1) <= 512

@@ -249,6 +249,19 @@ def test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(heads, 
     assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, kernel)
 
 
+def test_attention_too_wide_for_the_pass_over_the_keys():
+    """120 heads (of 8, padded to 32): 3840 columns of keys are more than the pass over the keys holds; 1156 keys per query
+    would ask for it."""
+    desc = workloads.ModelDesc(layers=2, d=960, heads=120, mlp=256, patch=14, tpatch=1, merge=1)
+    rng = np.random.default_rng(120)
+    items = [workloads.Item(workloads.IMAGE, 1, 476, 476, 476, 476, workloads.random_frames(rng, 1, 476, 476))]
+    wl = workloads.Workload("wide", desc, items, workloads.make_weights(desc, 33, random_affine=True))
+    ref = oracle.run(wl, workers=4)
+    enc, pl, patches, hidden, out = run_gpu(wl)
+    assert B.tcmv_plan_key_norms(pl.handle, 0) == 0
+    assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, "wide attention")
+
+
 @pytest.mark.parametrize("dh", [80, 64])
 def test_windows_of_up_to_64_tokens_with_ragged_edges(dh):
     """Windows of 8 x 8 patches on grids that are not multiples of 8: window sizes 64, 48, 32, 24, 16, 8 ... in
