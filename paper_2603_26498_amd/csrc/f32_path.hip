@@ -221,13 +221,16 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const float* vp = V + (size_t)(w.seg_start + min(j0 + 4 * lg + v, w.seg_len - 1)) * a.ldv + lr;
-      // zero past the end of the segment: the last row, which is read there, may hold an infinity, and 0 * inf is NaN
-      const bool key = j0 + 4 * lg + v < w.seg_len;
 #pragma unroll
-      for (int i = 0; i < ND; ++i) {
-        const float x = vp[16 * i];
-        vf[v][i] = key ? x : 0.f;
-      }
+      for (int i = 0; i < ND; ++i) vf[v][i] = vp[16 * i];
+    }
+    if (j0 + 16 > w.seg_len) {
+      // past the end of the segment the last row was read, which may hold an infinity, and 0 * inf is NaN
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+          if (j0 + 4 * lg + v >= w.seg_len) vf[v][i] = 0.f;
     }
     f32v4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
