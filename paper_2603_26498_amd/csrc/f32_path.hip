@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
     }
   }
   float m = -INFINITY, l = 0.f;
-  for (int j0 = wave * 16; j0 < w.seg_len; j0 += 64) {
+  for (int j0 = __builtin_amdgcn_readfirstlane(wave) * 16; j0 < w.seg_len; j0 += 64) {      // scalar: so are its conditions
     const float* kp = K + (size_t)(w.seg_start + min(j0 + lr, w.seg_len - 1)) * a.ldqk + lg * (DH / 4);
     f32v4 kf[ND];
     float vf[4][ND];
