@@ -878,23 +878,24 @@ enum GemmKernel { GK_INVALID, GK_P320, GK_P256, GK_T192x256, GK_T256x160, GK_T25
 // elements of k.  Those with shared = 0 fill a CU's LDS: they run in rounds of 256 tiles, and each round after the first
 // costs `more` on top.  Of the shared ones two (T128) or three (T64) run on a CU; the cost of a k-tile grows with the tiles
 // per CU from a floor, the memory latency (`more`).  Products that accumulate read and write four bytes per element:
-// 12.6 us for a 256x256 tile on a CU of its own (all CUs write out together), 0.9 where other tiles compute meanwhile.
-// Fitted to 933 products of fewer than 400 tiles of 256x256: every layer product of five encoders at 64 .. 23184 rows,
+// 12.4 us for a 256x256 tile on a CU of its own (all CUs write out together), 0.8 where other tiles compute meanwhile.
+// Fitted to 1373 products of fewer than 400 tiles of 256x256: every layer product of five encoders at 64 .. 23184 rows,
 // measured inside passes over 12 layers, whose weights come from memory (they exceed the last-level cache), and single
-// products with k from 128 to 8192 over weights that do too.  The kernel with the lowest estimate is on average 0.5 % slower
-// than the fastest (more than 5 % on 31 products, more than 10 % on 6); the estimates themselves are off by 15 % r.m.s.
+// products over weights that do too, with k from 128 to 8192 and at random row counts.  The kernel with the lowest estimate
+// is on average 0.5 % slower than the fastest (more than 5 % on 47 products, more than 10 % on 9); the estimates themselves
+// are off by 14 % r.m.s.
 struct TileKernel { GemmKernel kernel; int bm, bn, wave_n, shared; float base, per_k, more; };
 constexpr TileKernel kTileKernels[] = {
-    {GK_P320, 256, 320, 160, 0, 6.9f, 1.75f, 0.f},      {GK_P256, 256, 256, 64, 0, 3.5f, 1.51f, 4.4f},
-    {GK_T192x256, 192, 256, 128, 0, 9.3f, 1.30f, 0.2f}, {GK_T256x160, 256, 160, 160, 0, 5.1f, 1.05f, 2.8f},
-    {GK_T256x128, 256, 128, 64, 0, 4.2f, 0.79f, 5.5f},  {GK_T128x160, 128, 160, 160, 0, 9.0f, 0.57f, 0.f},
-    {GK_T128K2, 128, 128, 64, 0, 4.7f, 0.44f, 1.0f},    {GK_T128, 128, 128, 64, 1, 3.1f, 0.55f, 0.81f},
-    {GK_T64, 64, 64, 32, 1, 3.2f, 0.22f, 0.35f}};
+    {GK_P320, 256, 320, 160, 0, 7.7f, 1.63f, 0.f},       {GK_P256, 256, 256, 64, 0, 3.7f, 1.54f, 3.2f},
+    {GK_T192x256, 192, 256, 128, 0, 10.1f, 1.27f, 1.2f}, {GK_T256x160, 256, 160, 160, 0, 5.3f, 1.07f, 1.8f},
+    {GK_T256x128, 256, 128, 64, 0, 4.3f, 0.81f, 5.2f},   {GK_T128x160, 128, 160, 160, 0, 8.2f, 0.59f, 0.f},
+    {GK_T128K2, 128, 128, 64, 0, 4.5f, 0.47f, 1.6f},     {GK_T128, 128, 128, 64, 1, 3.3f, 0.56f, 0.76f},
+    {GK_T64, 64, 64, 32, 1, 3.3f, 0.22f, 0.33f}};
 
 float tile_cost(const TileKernel& t, int64_t m, int n, int k, int slices, bool accumulates) {
   const int64_t tiles = ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn) * slices;
   const float per_cu = (float)((tiles + 255) / 256), nk = (float)(k / 64 / slices);
-  const float out = accumulates ? (t.shared ? 0.9f : 12.6f) * (float)(t.bm * t.bn) / 65536.f : 0.f;
+  const float out = accumulates ? (t.shared ? 0.8f : 12.4f) * (float)(t.bm * t.bn) / 65536.f : 0.f;
   return t.shared ? t.base + nk * std::max(t.more, t.per_k * per_cu) + per_cu * out
                   : per_cu * (t.base + nk * t.per_k + out) + (per_cu - 1.f) * t.more;
 }
@@ -962,7 +963,7 @@ GemmKernel choose_kernel(const GemmArgs& a, int* wave_tile_n, int* block_n) {
     const float elements = 1e-6f * (float)a.m * (float)a.n;
     for (const TileKernel& t : kTileKernels) {
       if (!t.shared) continue;
-      const float c = tile_cost(t, a.m, a.n, a.k, 4, false) + (a.defer_reduce ? 0.75f : 3.65f) + (t.kernel == GK_T64 ? 4.f : 3.5f) * elements;
+      const float c = tile_cost(t, a.m, a.n, a.k, 4, false) + (a.defer_reduce ? 0.f : 2.9f) + (t.kernel == GK_T64 ? 5.f : 4.5f) * elements;
       if (c < best_cost) { best_cost = c; split = t.kernel == GK_T64 ? GK_SPLIT64 : GK_SPLIT128; }
     }
     if (split != GK_INVALID) return split;

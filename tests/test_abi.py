@@ -257,7 +257,7 @@ def test_route_queries_answer_on_the_host():
     (B.EPI_GATED, 576, 8192, 1024, "256x128"), (B.EPI_GATED, 640, 8192, 1024, "256x128"), (B.EPI_GELU, 1280, 4096, 1024, "256x128"),
     (B.EPI_RESID, 8192, 1024, 128, "128x128"), (B.EPI_RESID, 10240, 1024, 1024, "128x128"), (B.EPI_RESID, 11520, 1024, 1024, "128x128"),
     (B.EPI_RESID, 8464, 1280, 1280, "128x128"), (B.EPI_RESID, 9216, 1152, 1280, "128x128"), (B.EPI_RESID, 2304, 1280, 1280, "64x64"),
-    (B.EPI_RESID, 2688, 1024, 1024, "64x64"), (B.EPI_RESID, 10240, 1152, 4352, "128x128 k/2")])
+    (B.EPI_RESID, 2688, 1024, 1024, "64x64"), (B.EPI_RESID, 10240, 1152, 4352, "128x128")])
 def test_kernels_of_products_that_an_estimate_got_wrong(epi, m, n, k, kernel):
     assert B.tcmv_op_gemm_kernel(epi, m, n, k) == kernel
 
