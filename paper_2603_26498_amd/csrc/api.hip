@@ -576,15 +576,16 @@ int tcmv_plan_create(tcmv_ctx* ctx, const tcmv_item* items, int n_items, tcmv_pl
   // A small request (128-row items that do not give every CU two workgroups) waits for memory and barriers more than for
   // the vector unit: the reference-free loop then saves 0.1 us for every 64 keys where an item has a CU to itself and 0.28
   // where two share one, against 4.6 us for the second launch and the key norms (nearly free in the QKV product for heads
-  // of 64; a worse tile or a pass of 7 us for heads of 80, a pass for the others).  Measured over 332 such requests, whole
-  // layers, this rule loses at most 2 % against the better choice: 4 heads of 32, 14400 keys 280 us without, 227 with; 16 of 64,
-  // 2112 keys 151 / 147, 1280 keys 107 / 110; 16 of 80, 1152 keys 127 / 128; 4 of 96, 14400 keys 487 / 434, 4096 keys 134 / 138.
+  // of 64; a worse tile or a pass of about 10 us for heads of 80, a pass for the others).  Measured over 332 such requests,
+  // whole layers, this rule loses at most 2.4 % against the better choice: 4 heads of 32, 14400 keys 280 us without, 227 with; 16
+  // of 64, 2112 keys 151 / 147, 1280 keys 107 / 110; 16 of 80, 1152 keys 127 / 128, 3136 keys 242 / 247; 4 of 96, 14400 keys
+  // 487 / 434, 4096 keys 134 / 138.
   auto small_request_pays = [&]() {
     double rows = 0, pairs = 0;
     for (int64_t n : seg_len) { rows += (double)n; pairs += (double)n * (double)n; }
     const int dh = head_dim_of(d);
     const double items = (double)p->work.size() * d.heads;
-    const double cost = dh == 64 ? 5.0 : dh == 80 ? 12.0 : 6.0 + 0.008 * (double)attn_width_of(d);
+    const double cost = dh == 64 ? 5.0 : dh == 80 ? 16.0 : 6.0 + 0.008 * (double)attn_width_of(d);
     return pairs / 64.0 * (items > 256 ? 0.28 : 0.1) >= cost * rows;
   };
   const bool small_request = p->bq == 128 && (int64_t)p->work.size() * d.heads < 512;
