@@ -42,7 +42,7 @@ __device__ __forceinline__ void store_f32(const GemmArgs& g, int64_t row, int co
 // its four waves in chunks of 16, no staging (operands go straight from the caches to registers,
 // all loads of four chunks in flight together), partial sums added through LDS in wave order.
 // Such a product is bound by latency, not by arithmetic: what counts is many workgroups and one
-// memory round trip.  197 rows, one layer's products: 3.0 - 5.7 us each (35 - 85 us with 64x64 tiles on the
+// memory round trip.  197 rows, one layer's products: 3 - 8 us each in a pass (35 - 85 us with 64x64 tiles on the
 // vector ALU).
 // ---------------------------------------------------------------------------
 template <int EPI>
@@ -186,7 +186,7 @@ hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
 // tiles of 16 keys are dealt out to the waves, each keeps its own online softmax, and the four
 // partial results meet in LDS.  S^T = K Q^T leaves a lane with one query (lane & 15) and four keys
 // (4 * (lane >> 4) + v), which is the B operand of O^T += V^T P^T as it stands.  A small request is bound by
-// latency: 197 tokens, 4 heads of 64 are 52 workgroups of four waves with at most four key tiles each (9.8 us;
+// latency: 197 tokens, 4 heads of 64 are 52 workgroups of four waves with at most four key tiles each (9.6 us;
 // 273 us with one thread per query walking all keys).
 // ---------------------------------------------------------------------------
 template <int DH>

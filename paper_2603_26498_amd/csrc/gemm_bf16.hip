@@ -36,7 +36,8 @@
 // requested one iteration ahead) and the bytes that go from L2 to LDS (128x128 tiles: 11 TB/s at 700 TFLOP/s), so
 // these kernels keep up to four stages in flight and the tiles that fill LDS once per CU may let two waves share a
 // sub-tile, each with half of the k-steps: the wave tiles stay large (64x160: 7 fragment reads for 10 MFMAs) where the
-// workgroup's is small.  4096 x 1280 x 5120: 79 -> 63 us; 256 x 3840 x 1280: 11.8 -> 8.0; 64 x 5120 x 5120: 58 -> 33.
+// workgroup's is small.  With weights from memory, against two stages and 128x128 or 64x64 tiles only: 4096 x 1280 x 5120
+// 79 -> 63 us; 256 x 3840 x 1280 18.4 -> 11.5; 64 x 5120 x 5120 57 -> 34.
 // A long contraction over few rows that accumulates into the residual stream is cut into four slices of k whose
 // fp32 partial sums a second kernel, or the norm that reads the stream next, adds in slice order.
 //

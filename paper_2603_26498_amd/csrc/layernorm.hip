@@ -4,9 +4,10 @@
 // mean and the centred sum of squares are reduced across the wave in fp32 (two
 // passes over registers, no second trip to memory); the result is written as
 // bf16 or fp32.  HBM-bound: 4*d bytes read + 2*d (or 4*d) bytes written per row.
-// All loads, gamma and beta too, are requested before the first is used, at clamped indices instead of under a
-// condition: under one, every column group waited for its gamma and beta and, the counter being the same, for the
-// stores of the group before (1280 wide: 256 rows 4.7 -> 3.8 us, 16656 rows 23.3 -> 21.7).
+// The loads of a row are requested together, at clamped indices instead of under a condition, and gamma and beta are not
+// read column group by column group behind the stores of the group before (1280 wide: 256 rows 4.7 -> 3.7 us, 16656 rows
+// 23.3 -> 21.8).  The compiler moves the loads of gamma and beta behind the first reduction, though, so one more memory
+// round trip stays exposed; only the kernel for sliced products below has everything on its way before it uses anything.
 #include "tcmv_internal.h"
 #include "device_utils.h"
 
@@ -87,10 +88,11 @@ static hipError_t launch_ln_t(const float* x, const float* g, const float* b, vo
 }
 
 // The same over rows that are first completed by the four fp32 partial sums of the product before (bias + slice 0 + .. +
-// slice 3, the order of the separate reduction): saves that kernel's launch and its trip through x.  Only requests of a
-// few hundred rows come here, bound by latency and by what one CU can fetch, so a row gets a workgroup of its own and
-// everything it needs, gamma and beta too, is requested before anything is used.  256 x 1280: 4.2 us against
-// 4.4 + 4.7 in two kernels (11.3 with a wavefront per row).
+// slice 3, the order of the separate reduction): saves that kernel's launch and its trip through x.  Requests come here
+// whose products are cut along k, at 1280 columns up to 580 rows behind the out-projection and up to 1550 behind fc2: bound
+// by latency and, towards the upper end, by the slices (1120 rows 7.6 us).  A row gets a workgroup of its own and
+// everything it needs, gamma and beta too, is requested before anything is used.  256 x 1280: 4.3 us against 4.4 + 4.7 in
+// two kernels (11.3 with a wavefront per row).
 template <int NV, bool OUT_BF16, bool RMS>
 __global__ __launch_bounds__(256) void layernorm_slices_kernel(float* x, const float* __restrict__ partial,
                                                                const float* __restrict__ bias, const float* __restrict__ gamma,
