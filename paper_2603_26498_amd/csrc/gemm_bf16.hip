@@ -873,7 +873,7 @@ static hipError_t launch_persist(const GemmArgs& a, hipStream_t s) {
 
 
 namespace {
-enum GemmKernel { GK_INVALID, GK_P320, GK_P256, GK_T192x256, GK_T256x160, GK_T256x128, GK_T128x160, GK_T128K2, GK_T128, GK_T64, GK_SPLIT128, GK_SPLIT64 };
+enum GemmKernel { GK_INVALID, GK_P320, GK_P256, GK_T192x256, GK_T256x160, GK_T256x128, GK_T128x160, GK_T128K2, GK_T128, GK_T64, GK_SPLIT128, GK_SPLIT64, GK_COUNT };
 
 // Tile kernels and what one workgroup's tile costs: `base` microseconds (first loads, write-out) plus `per_k` for every 64
 // elements of k.  Those with shared = 0 fill a CU's LDS: they run in rounds of 256 tiles, and each round after the first
@@ -907,15 +907,56 @@ bool wave_tile_holds_heads(int wave_n, int qcols, int dh) {
 }
 
 bool is_persistent(GemmKernel k) { return k == GK_P320 || k == GK_P256; }
+bool is_sliced(GemmKernel k) { return k == GK_SPLIT128 || k == GK_SPLIT64; }
 
-// which kernel a product runs on, and the width of its wave tiles
-GemmKernel choose_kernel(const GemmArgs& a, int* wave_tile_n, int* block_n) {
-  if (a.k <= 0 || a.k % 64 || a.lda % 8 || a.n <= 0 || a.n % 8 || a.ldc % 4) return GK_INVALID;
-  if (a.epi == EPI_QKV && (a.split % 8)) return GK_INVALID;
-  if (a.epi == EPI_QKV && a.rope && (a.rope_dh % 8 || a.rope_dh <= 0)) return GK_INVALID;
-  if (a.epi == EPI_GATED && (a.ldc % 4)) return GK_INVALID;
+// Which kernel computes rows [0, rows) of a product and which the rows behind them, and the widths of their wave tiles and tiles.
+struct GemmPart { GemmKernel kernel = GK_INVALID; int wave_n = 0, block_n = 0; };
+struct GemmRoute { GemmPart first, rest; int64_t rows = 0; bool valid() const { return first.kernel != GK_INVALID; } };
+
+// what key norms add: a tile that cannot compute them pays for the separate pass over the keys (12 - 20 us), one that can
+// for the sums in its write-out (1 - 14 us; they grow with the rows and more with the smaller tiles)
+float norm_cost(const GemmArgs& a, const TileKernel& t, int64_t m) {
+  if (a.epi != EPI_QKV || !a.kn_dh) return 0.f;
+  if (!wave_tile_holds_heads(t.wave_n, a.qcols, a.kn_dh) || (is_persistent(t.kernel) && a.n % t.bn)) return 13.f + 2e-4f * (float)m;
+  return is_persistent(t.kernel) ? 3.f + 2e-4f * (float)m : 1.f + 5e-4f * (float)m;
+}
+
+// Estimate for a persistent kernel over whole rounds of tiles, where tile_cost falls short (the chip clocks lower when every
+// CU computes): microseconds a round, by k-tiles and by what the write-out does, and for the last, partly filled round.
+// Fitted to 2400 products of 3000 - 102000 rows.
+struct RoundCost { float base, full_k, part_k, part_k_fill, gelu, resid, qkv, gated; };
+constexpr RoundCost kRoundCosts[] = {{6.1f, 2.13f, 1.01f, 0.97f, 6.9f, 18.5f, 6.3f, 5.3f}, {3.5f, 1.95f, 0.98f, 0.93f, 1.2f, 15.6f, 1.2f, 0.f}};
+
+float rounds_cost(const GemmArgs& a, const TileKernel& t, int64_t m) {
+  const RoundCost& c = kRoundCosts[t.kernel == GK_P320 ? 0 : 1];
+  const int64_t tiles = ((m + t.bm - 1) / t.bm) * ((a.n + t.bn - 1) / t.bn);
+  const float full = (float)(tiles / 256), fill = (float)(tiles % 256) / 256.f, part = fill > 0.f ? 1.f : 0.f, nk = (float)(a.k / 64);
+  const float out = a.epi == EPI_RESID ? c.resid : a.epi == EPI_QKV ? c.qkv : a.epi == EPI_GATED ? c.gated : c.gelu;
+  return c.base + nk * (full * c.full_k + part * (c.part_k + fill * c.part_k_fill)) + (full + 0.7f * part) * out + norm_cost(a, t, m);
+}
+
+// the kernel with the lowest estimate for `m` rows
+const TileKernel* cheapest_tile(const GemmArgs& a, int64_t m, bool can_persist, float* cost) {
+  const TileKernel* best = nullptr;
+  for (const TileKernel& t : kTileKernels) {
+    if (is_persistent(t.kernel) && (!can_persist || m < 256)) continue;
+    const float c = tile_cost(t, m, a.n, a.k, 1, a.epi == EPI_RESID) + norm_cost(a, t, m);
+    if (!best || c < *cost) { best = &t; *cost = c; }
+  }
+  return best;
+}
+
+GemmPart part(const TileKernel& t) { return {t.kernel, t.wave_n, t.bn}; }
+
+GemmRoute choose_route(const GemmArgs& a) {
+  GemmRoute r;
+  if (a.k <= 0 || a.k % 64 || a.lda % 8 || a.n <= 0 || a.n % 8 || a.ldc % 4) return r;
+  if (a.epi == EPI_QKV && (a.split % 8)) return r;
+  if (a.epi == EPI_QKV && a.rope && (a.rope_dh % 8 || a.rope_dh <= 0)) return r;
+  if (a.epi == EPI_GATED && (a.ldc % 4)) return r;
   // operand element offsets are kept in 32 bits
-  if ((double)a.m * (double)a.lda >= 4294967296.0 || (double)a.n * (double)a.k >= 4294967296.0) return GK_INVALID;
+  if ((double)a.m * (double)a.lda >= 4294967296.0 || (double)a.n * (double)a.k >= 4294967296.0) return r;
+  r.rows = a.m;
   // The persistent kernels shift their last tile back to the matrix edge and address their operands in bytes, 32 bits.
   const bool can_persist = a.k >= 128 && a.m >= 256 && a.n >= 320 && a.epi != EPI_PARTIAL &&
                            (double)a.m * (double)a.lda < 2147483648.0 && (double)a.n * (double)a.k < 2147483648.0;
@@ -923,6 +964,7 @@ GemmKernel choose_kernel(const GemmArgs& a, int* wave_tile_n, int* block_n) {
   // CUs.  A tile 320 columns wide is taken where it needs no more tile area x rounds than a 256-wide one (hidden
   // sizes that are multiples of 320 but not of 256, such as 1280).
   const int64_t big_tiles = ((a.m + 255) / 256) * ((a.n + 255) / 256);
+  float cost = 0.f;
   if (big_tiles >= 400 && can_persist) {
     auto area = [&](int64_t bm, int64_t bn) {
       const int64_t t = ((a.m + bm - 1) / bm) * ((a.n + bn - 1) / bn);
@@ -933,43 +975,63 @@ GemmKernel choose_kernel(const GemmArgs& a, int* wave_tile_n, int* block_n) {
     // keys takes 21 us at 25772 rows with heads of 64, the square tiles 10 - 15 more than the 184 of the wide ones
     const bool norms = a.epi == EPI_QKV && a.kn_dh && wide == square && a.n % 256 == 0 && wave_tile_holds_heads(64, a.qcols, a.kn_dh) &&
                        !wave_tile_holds_heads(160, a.qcols, a.kn_dh);
-    if (wide <= square && !norms) { *wave_tile_n = 160; *block_n = 320; return GK_P320; }
-    *wave_tile_n = 64; *block_n = 256;
-    return GK_P256;
-  }
-  // Smaller products: a few rounds of tiles at most, so the round that is only partly filled decides.  The kernel with
-  // the lowest estimate is taken (4096 x 1280 x 5120: 63 us with 128x160 tiles, 79 with 128x128; 4096 x 5120 x 1280:
-  // 54 with one round of 256x320 tiles, 75 with 128x128; 256 x 5120 x 1280: 16 with 64x64, 19 - 45 with larger tiles).
-  // Where key norms are wanted (kn_dh), a tile that cannot compute them pays for the separate pass over the keys (12 - 20
-  // us), one that can for the sums in its write-out (1 - 14 us; they grow with the rows and more with the smaller tiles).
-  const TileKernel* best = nullptr;
-  float best_cost = 0.f;
-  for (const TileKernel& t : kTileKernels) {
-    if (is_persistent(t.kernel) && !can_persist) continue;
-    float c = tile_cost(t, a.m, a.n, a.k, 1, a.epi == EPI_RESID);
-    if (a.epi == EPI_QKV && a.kn_dh) {
-      if (!wave_tile_holds_heads(t.wave_n, a.qcols, a.kn_dh) || (is_persistent(t.kernel) && a.n % t.bn)) c += 13.f + 2e-4f * (float)a.m;
-      else c += is_persistent(t.kernel) ? 3.f + 2e-4f * (float)a.m : 1.f + 5e-4f * (float)a.m;
+    const TileKernel& t = kTileKernels[wide <= square && !norms ? 0 : 1];
+    r.first = part(t);
+    cost = tile_cost(t, a.m, a.n, a.k, 1, a.epi == EPI_RESID) + norm_cost(a, t, a.m);
+  } else {
+    // Smaller products: a few rounds of tiles at most, so the round that is only partly filled decides.  The kernel with
+    // the lowest estimate is taken (4096 x 1280 x 5120: 63 us with 128x160 tiles, 79 with 128x128; 4096 x 5120 x 1280:
+    // 54 with one round of 256x320 tiles, 75 with 128x128; 256 x 5120 x 1280: 16 with 64x64, 19 - 45 with larger tiles).
+    r.first = part(*cheapest_tile(a, a.m, can_persist, &cost));
+    // A contraction over few rows that accumulates (out-projection and fc2 of one small request): a quarter of k per
+    // workgroup, added to C in a fixed order by a second kernel or by the norm that follows (defer_reduce), where that is
+    // estimated to win in spite of it.  What it costs, the slices written and read again, grows with the output: measured
+    // with the longer norm, 256 x 1280 x 1280 7 us against 10 unsplit, 576 rows 9.5 / 9.7; 256 x 1280 x 5120 14 / 30, 1024
+    // rows 30 (128x128 tiles) / 42, 1440 rows 33 / 41, 1760 rows 48 / 48.
+    if (a.epi == EPI_RESID && a.partial && a.k >= (a.defer_reduce ? 1024 : 2048) && (a.k / 64) % 4 == 0) {
+      const float elements = 1e-6f * (float)a.m * (float)a.n;
+      for (const TileKernel& t : kTileKernels) {
+        if (!t.shared) continue;
+        const float c = tile_cost(t, a.m, a.n, a.k, 4, false) + (a.defer_reduce ? 0.f : 2.9f) + (t.kernel == GK_T64 ? 5.f : 4.5f) * elements;
+        if (c < cost) { cost = c; r.first.kernel = t.kernel == GK_T64 ? GK_SPLIT64 : GK_SPLIT128; }
+      }
     }
-    if (!best || c < best_cost) { best = &t; best_cost = c; }
   }
-  *wave_tile_n = best->wave_n; *block_n = best->bn;
-  // A contraction over few rows that accumulates (out-projection and fc2 of one small request): a quarter of k per
-  // workgroup, added to C in a fixed order by a second kernel or by the norm that follows (defer_reduce), where that is
-  // estimated to win in spite of it.  What it costs, the slices written and read again, grows with the output: measured
-  // with the longer norm, 256 x 1280 x 1280 7 us against 10 unsplit, 576 rows 9.5 / 9.7; 256 x 1280 x 5120 14 / 30, 1024
-  // rows 30 (128x128 tiles) / 42, 1440 rows 33 / 41, 1760 rows 48 / 48.
-  if (a.epi == EPI_RESID && a.partial && a.k >= (a.defer_reduce ? 1024 : 2048) && (a.k / 64) % 4 == 0) {
-    GemmKernel split = GK_INVALID;
-    const float elements = 1e-6f * (float)a.m * (float)a.n;
-    for (const TileKernel& t : kTileKernels) {
-      if (!t.shared) continue;
-      const float c = tile_cost(t, a.m, a.n, a.k, 4, false) + (a.defer_reduce ? 0.f : 2.9f) + (t.kernel == GK_T64 ? 5.f : 4.5f) * elements;
-      if (c < best_cost) { best_cost = c; split = t.kernel == GK_T64 ? GK_SPLIT64 : GK_SPLIT128; }
+  // Products with at least one whole round of large tiles: a last round that is nearly empty takes about half as long as a
+  // full one, more than the rows in it take as a product of their own.  Both persistent kernels, whole or cut behind their
+  // whole rounds, against what was chosen so far; cut where that is estimated to win by 3 % and 3 us (the estimates are off
+  // by 4.5 % r.m.s.; of 1200 products of 3000 - 102000 rows, 211 are cut, seven of them to a loss of 2 - 5 %; with the best
+  // of all measured routes 2.4 % would be gained on average, with this rule 1.6 %).  16656 rows: fc2 (1280 x 5120) 242 -> 212 us,
+  // out-projection 79.7 -> 73.8, fc1 224 -> 210; 23501 rows: fc2 352 -> 307; 18464 x 1024 x 4096 170 -> 165.
+  if (can_persist && !is_sliced(r.first.kernel)) {
+    float best = is_persistent(r.first.kernel) ? rounds_cost(a, kTileKernels[r.first.kernel - GK_P320], a.m) : cost;
+    best *= 0.97f;
+    const bool persistent = big_tiles >= 400;
+    for (int i = 0; i < 2; ++i) {
+      const TileKernel& t = kTileKernels[i];
+      const int64_t tiles_n = (a.n + t.bn - 1) / t.bn, whole = (a.m / 256) * tiles_n / 256;   // whole rounds
+      if (persistent && r.first.kernel != t.kernel && !a.kn_dh) {
+        const float c = rounds_cost(a, t, a.m);
+        if (c < best) { best = c; r.first = part(t); r.rows = a.m; }
+      }
+      const int64_t rows = whole * 256 / tiles_n * 256;
+      if (rows <= 0 || rows >= a.m) continue;
+      float c_rest = 0.f;
+      const TileKernel* rest = cheapest_tile(a, a.m - rows, true, &c_rest);
+      if (is_persistent(rest->kernel)) c_rest = rounds_cost(a, *rest, a.m - rows);
+      const float c = rounds_cost(a, t, rows) + c_rest + 3.f;
+      if (c < best) { best = c; r.first = part(t); r.rest = part(*rest); r.rows = rows; }
     }
-    if (split != GK_INVALID) return split;
   }
-  return best->kernel;
+  return r;
+}
+
+bool computes_key_norms(const GemmPart& p, const GemmArgs& a) {
+  // whole heads per wave tile, wave tiles that start at head boundaries, no shifted last tile
+  return wave_tile_holds_heads(p.wave_n, a.qcols, a.kn_dh) && (!is_persistent(p.kernel) || a.n % p.block_n == 0);
+}
+bool computes_key_norms(const GemmRoute& r, const GemmArgs& a) {
+  return r.valid() && computes_key_norms(r.first, a) && (r.rows == a.m || computes_key_norms(r.rest, a));
 }
 }  // namespace
 
@@ -977,33 +1039,23 @@ bool gemm_bf16_can_fuse_key_norms(int64_t m, int n, int k, int qcols, int dh) {
   if (dh != 64 && dh != 80) return false;
   GemmArgs a{};
   a.m = m; a.n = n; a.k = k; a.lda = k; a.ldc = 2 * qcols; a.epi = EPI_QKV; a.split = 2 * qcols; a.qcols = qcols; a.kn_dh = dh;
-  int tn = 0, bn = 0;
-  const GemmKernel gk = choose_kernel(a, &tn, &bn);
-  // whole heads per wave tile, wave tiles that start at head boundaries, no shifted last tile
-  return gk != GK_INVALID && wave_tile_holds_heads(tn, qcols, dh) && (!is_persistent(gk) || n % bn == 0);
+  return computes_key_norms(choose_route(a), a);
 }
 
 const char* gemm_bf16_kernel_name(const GemmArgs& a) {
-  static const char* const names[] = {nullptr, "256x320 persistent", "256x256 persistent", "192x256", "256x160", "256x128", "128x160",
-                                      "128x128 k/2", "128x128", "64x64", "128x128 slices", "64x64 slices"};   // GemmKernel order
-  int tn = 0, bn = 0;
-  return names[choose_kernel(a, &tn, &bn)];
+  // GemmKernel order; then whole rounds of either persistent kernel followed by another for the rest
+#define TCMV_NAMES(first) {first "256x320 persistent", first "256x256 persistent", first "192x256", first "256x160", first "256x128", \
+                           first "128x160", first "128x128 k/2", first "128x128", first "64x64", first "128x128 slices", first "64x64 slices"}
+  static const char* const names[3][GK_COUNT - 1] = {TCMV_NAMES(""), TCMV_NAMES("256x320 persistent + "), TCMV_NAMES("256x256 persistent + ")};
+#undef TCMV_NAMES
+  const GemmRoute r = choose_route(a);
+  if (!r.valid()) return nullptr;
+  return r.rows == a.m ? names[0][r.first.kernel - 1] : names[r.first.kernel == GK_P320 ? 1 : 2][r.rest.kernel - 1];
 }
 
-int gemm_bf16_slices(const GemmArgs& a) {
-  int tn = 0, bn = 0;
-  const GemmKernel gk = choose_kernel(a, &tn, &bn);
-  return gk == GK_SPLIT128 || gk == GK_SPLIT64 ? 4 : 1;
-}
+int gemm_bf16_slices(const GemmArgs& a) { return is_sliced(choose_route(a).first.kernel) ? 4 : 1; }
 
-hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
-  if (a.m == 0 || a.n == 0) return hipSuccess;
-  int tn = 0, bn = 0;
-  const GemmKernel gk = choose_kernel(a, &tn, &bn);
-  if (a.epi == EPI_QKV && a.kmax2 &&
-      !(gk != GK_INVALID && wave_tile_holds_heads(tn, a.qcols, a.kn_dh) && a.split == 2 * a.qcols && a.row_seg &&
-        (!is_persistent(gk) || a.n % bn == 0)))
-    return hipErrorInvalidValue;
+static hipError_t launch_part(GemmKernel gk, const GemmArgs& a, hipStream_t s) {
   if (is_persistent(gk) && a.epi == EPI_RESID && (double)a.m * (double)a.n * 4.0 > 400e6) {
     GemmArgs g = a;                                 // an output larger than the last-level cache: see wave_epilogue
     g.epi = EPI_RESID_AHEAD;
@@ -1032,6 +1084,33 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
     case GK_T64: return launch_cfg<64, 64, 2, 2, 1, 3, 3>(a, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+// the product of rows [r0, m): every operand and output that has a row per row of A
+static GemmArgs rows_from(const GemmArgs& a, int64_t r0) {
+  GemmArgs g = a;
+  const bool f32_out = a.epi == EPI_RESID || a.epi == EPI_EMBED;
+  g.m = a.m - r0;
+  g.a = reinterpret_cast<const uint16_t*>(a.a) + r0 * a.lda;
+  if (!(a.epi == EPI_EMBED && a.dst_row)) g.c = reinterpret_cast<uint8_t*>(a.c) + r0 * a.ldc * (f32_out ? 4 : 2);
+  if (a.dst_row) g.dst_row = a.dst_row + r0;
+  if (a.pos_idx) g.pos_idx = a.pos_idx + r0;
+  if (a.vcol) g.vcol = a.vcol + r0;
+  if (a.rope) g.rope = a.rope + r0 * a.rope_dh;
+  if (a.row_seg) g.row_seg = a.row_seg + r0;
+  return g;
+}
+
+hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
+  if (a.m == 0 || a.n == 0) return hipSuccess;
+  const GemmRoute r = choose_route(a);
+  if (a.epi == EPI_QKV && a.kmax2 && !(computes_key_norms(r, a) && a.split == 2 * a.qcols && a.row_seg)) return hipErrorInvalidValue;
+  if (!r.valid()) return hipErrorInvalidValue;
+  if (r.rows == a.m) return launch_part(r.first.kernel, a, s);
+  GemmArgs head = a;
+  head.m = r.rows;
+  const hipError_t e = launch_part(r.first.kernel, head, s);
+  return e != hipSuccess ? e : launch_part(r.rest.kernel, rows_from(a, r.rows), s);
 }
 
 }  // namespace tcmv

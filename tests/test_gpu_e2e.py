@@ -249,6 +249,11 @@ def test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(heads, 
     assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, kernel)
 
 
+def test_qkv_product_in_whole_rounds_and_the_rest():
+    """Rotary factors, transposed values and key norms of the rows behind the whole rounds, which a second kernel computes."""
+    test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(8, 64, (31, 37), 19, "256x256 persistent + 128x128", 0.36)
+
+
 def test_attention_too_wide_for_the_pass_over_the_keys():
     """120 heads (of 8, padded to 32): 3840 columns of keys are more than the pass over the keys holds; 1156 keys per query
     would ask for it."""

@@ -512,6 +512,15 @@ def test_gemm_bf16_tile_kernels(epi, m, n, k, kernel):
     (test_gated_epilogue if epi == B.EPI_GATED else test_gemm_bf16)(*((m, n, k) if epi == B.EPI_GATED else (m, n, k, epi)))
 
 
+@pytest.mark.parametrize("epi,m,n,k,kernel", [
+    (B.EPI_STORE, 12043, 2568, 448, "256x256 persistent + 64x64"), (B.EPI_GELU, 11949, 2568, 384, "256x256 persistent + 128x128"),
+    (B.EPI_RESID, 9233, 2568, 128, "256x256 persistent + 128x128"), (B.EPI_RESID, 17667, 3840, 128, "256x320 persistent + 64x64"),
+    (B.EPI_GATED, 12045, 2568, 576, "256x256 persistent + 64x64")])
+def test_gemm_bf16_whole_rounds_and_the_rest(epi, m, n, k, kernel):
+    """Whole rounds of large tiles for the first rows, another kernel for the ragged rest."""
+    test_gemm_bf16_tile_kernels(epi, m, n, k, kernel)
+
+
 @pytest.mark.parametrize("lens,qs,big_head", [([4096, 2048, 2048], 6.0, None), ([4096, 4096], 1.0, 3)])
 def test_attention_work_items_of_512_rows(lens, qs, big_head):
     """16 items of 512 rows for 16 heads, one for every CU: peaked scores, and the reference-free copy for all heads but one."""
