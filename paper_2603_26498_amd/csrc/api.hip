@@ -725,7 +725,11 @@ const char* tcmv_plan_gemm_kernel(const tcmv_plan* p, int kernel_class, int laye
   GemmArgs g = layer_product(p, kernel_class, layer);
   if (g.m <= 0) return nullptr;
   // only looked at for being there
-  if (g.epi == EPI_RESID && encode_ws(p).splitk_bytes) g.partial = reinterpret_cast<float*>(sizeof(float));
+  if (g.epi == EPI_RESID) {
+    const EncodeWs ws = encode_ws(p);
+    if (ws.splitk_bytes) g.partial = reinterpret_cast<float*>(sizeof(float));
+    else { g.rest_partial = reinterpret_cast<float*>(sizeof(float)); g.rest_floats = (int64_t)((ws.vt - ws.qkv) / sizeof(float)); }
+  }
   return gemm_bf16_kernel_name(g);
 }
 
@@ -828,6 +832,9 @@ int tcmv_encode(tcmv_ctx* ctx, const tcmv_plan* p, const void* d_meta, const voi
     if (ws.splitk_bytes) {
       g.partial = reinterpret_cast<float*>(wsb + ws.splitk);
       if (g.defer_reduce && gemm_bf16_slices(g) > 1) { slices = g.partial; slices_bias = g.bias; }
+    } else if (bf) {                               // queries and keys are not needed between the attention and the next layer
+      g.rest_partial = reinterpret_cast<float*>(qkv);
+      g.rest_floats = (int64_t)((ws.vt - ws.qkv) / sizeof(float));
     }
     return timed(ctx, cat, s, [&] { return run_gemm(ctx, g, s); });
   };

@@ -948,6 +948,17 @@ const TileKernel* cheapest_tile(const GemmArgs& a, int64_t m, bool can_persist, 
 
 GemmPart part(const TileKernel& t) { return {t.kernel, t.wave_n, t.bn}; }
 
+// four slices of k for `m` rows, taken if estimated below *cost; added by the norm that follows (`deferred`) or by a kernel
+void consider_slices(const GemmArgs& a, int64_t m, bool deferred, float* cost, GemmPart* chosen) {
+  if (a.epi != EPI_RESID || a.k < (deferred ? 1024 : 2048) || (a.k / 64) % 4) return;
+  const float elements = 1e-6f * (float)m * (float)a.n;
+  for (const TileKernel& t : kTileKernels) {
+    if (!t.shared) continue;
+    const float c = tile_cost(t, m, a.n, a.k, 4, false) + (deferred ? 0.f : 2.9f) + (t.kernel == GK_T64 ? 5.f : 4.5f) * elements;
+    if (c < *cost) { *cost = c; chosen->kernel = t.kernel == GK_T64 ? GK_SPLIT64 : GK_SPLIT128; }
+  }
+}
+
 GemmRoute choose_route(const GemmArgs& a) {
   GemmRoute r;
   if (a.k <= 0 || a.k % 64 || a.lda % 8 || a.n <= 0 || a.n % 8 || a.ldc % 4) return r;
@@ -988,21 +999,14 @@ GemmRoute choose_route(const GemmArgs& a) {
     // estimated to win in spite of it.  What it costs, the slices written and read again, grows with the output: measured
     // with the longer norm, 256 x 1280 x 1280 7 us against 10 unsplit, 576 rows 9.5 / 9.7; 256 x 1280 x 5120 14 / 30, 1024
     // rows 30 (128x128 tiles) / 42, 1440 rows 33 / 41, 1760 rows 48 / 48.
-    if (a.epi == EPI_RESID && a.partial && a.k >= (a.defer_reduce ? 1024 : 2048) && (a.k / 64) % 4 == 0) {
-      const float elements = 1e-6f * (float)a.m * (float)a.n;
-      for (const TileKernel& t : kTileKernels) {
-        if (!t.shared) continue;
-        const float c = tile_cost(t, a.m, a.n, a.k, 4, false) + (a.defer_reduce ? 0.f : 2.9f) + (t.kernel == GK_T64 ? 5.f : 4.5f) * elements;
-        if (c < cost) { cost = c; r.first.kernel = t.kernel == GK_T64 ? GK_SPLIT64 : GK_SPLIT128; }
-      }
-    }
+    if (a.partial) consider_slices(a, a.m, a.defer_reduce, &cost, &r.first);
   }
   // Products with at least one whole round of large tiles: a last round that is nearly empty takes about half as long as a
   // full one, more than the rows in it take as a product of their own.  Both persistent kernels, whole or cut behind their
   // whole rounds, against what was chosen so far; cut where that is estimated to win by 3 % and 3 us (the estimates are off
-  // by 4.5 % r.m.s.; of 1200 products of 3000 - 102000 rows, 211 are cut, seven of them to a loss of 2 - 5 %; with the best
-  // of all measured routes 2.4 % would be gained on average, with this rule 1.6 %).  16656 rows: fc2 (1280 x 5120) 242 -> 212 us,
-  // out-projection 79.7 -> 73.8, fc1 224 -> 210; 23501 rows: fc2 352 -> 307; 18464 x 1024 x 4096 170 -> 165.
+  // by 4.5 % r.m.s.; of 1200 products of 3000 - 102000 rows the best of all measured routes would gain 2.4 % on average, this
+  // rule gains 1.5 % and loses more than 2 % on four, 5.5 % at most).  16656 rows: fc2 (1280 x 5120) 242 -> 212 us, with the 272 rows behind
+  // the round in slices of k 200; fc1 224 -> 210; 23501 x 1280 x 5120 352 -> 307.
   if (can_persist && !is_sliced(r.first.kernel)) {
     float best = is_persistent(r.first.kernel) ? rounds_cost(a, kTileKernels[r.first.kernel - GK_P320], a.m) : cost;
     best *= 0.97f;
@@ -1019,8 +1023,11 @@ GemmRoute choose_route(const GemmArgs& a) {
       float c_rest = 0.f;
       const TileKernel* rest = cheapest_tile(a, a.m - rows, true, &c_rest);
       if (is_persistent(rest->kernel)) c_rest = rounds_cost(a, *rest, a.m - rows);
+      else if (a.epi == EPI_GELU || a.epi == EPI_QKV) c_rest *= rest->kernel == GK_T64 ? 1.1f : 1.25f;   // what tile_cost leaves out
+      GemmPart tail = part(*rest);
+      if (a.rest_partial && 4 * (a.m - rows) * a.n <= a.rest_floats) consider_slices(a, a.m - rows, false, &c_rest, &tail);
       const float c = rounds_cost(a, t, rows) + c_rest + 3.f;
-      if (c < best) { best = c; r.first = part(t); r.rest = part(*rest); r.rows = rows; }
+      if (c < best) { best = c; r.first = part(t); r.rest = tail; r.rows = rows; }
     }
   }
   return r;
@@ -1098,6 +1105,8 @@ static GemmArgs rows_from(const GemmArgs& a, int64_t r0) {
   if (a.vcol) g.vcol = a.vcol + r0;
   if (a.rope) g.rope = a.rope + r0 * a.rope_dh;
   if (a.row_seg) g.row_seg = a.row_seg + r0;
+  g.partial = a.rest_partial;
+  g.defer_reduce = 0;
   return g;
 }
 

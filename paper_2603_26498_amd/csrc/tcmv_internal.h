@@ -86,6 +86,9 @@ struct GemmArgs {
   // the slices stay in `partial` when the launcher cuts k (gemm_bf16_slices says whether it will): the caller hands
   // them to launch_layernorm_slices
   int defer_reduce;
+  // EPI_RESID with whole rounds of tiles and a few rows behind them: scratch (rest_floats values) in which the launcher may
+  // keep slices of those rows until a second kernel adds them
+  float* rest_partial; int64_t rest_floats;
 };
 
 struct AttnArgs {

@@ -251,7 +251,23 @@ def test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(heads, 
 
 def test_qkv_product_in_whole_rounds_and_the_rest():
     """Rotary factors, transposed values and key norms of the rows behind the whole rounds, which a second kernel computes."""
-    test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(8, 64, (31, 37), 19, "256x256 persistent + 128x128", 0.36)
+    test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(12, 64, (38, 35), 6, "256x256 persistent + 128x128 k/2", 0.36)
+
+
+def test_rows_behind_whole_rounds_in_slices_of_k():
+    """fc2 of 13440 rows: 13056 in whole rounds of tiles, the rest in four slices of k that wait in the buffer of the queries and
+    keys; run twice, equal bit for bit."""
+    desc = workloads.ModelDesc(layers=1, d=1600, heads=25, mlp=2304, patch=14, tpatch=1, merge=1)
+    rng = np.random.default_rng(41)
+    items = [workloads.Item(workloads.IMAGE, 1, 392, 336, 392, 336, workloads.random_frames(rng, 1, 392, 336)) for _ in range(20)]
+    wl = workloads.Workload("rest_in_slices", desc, items, workloads.make_weights(desc, 35, random_affine=True))
+    ref = oracle.run(wl, workers=4)
+    enc, pl, patches, hidden, out = run_gpu(wl)
+    assert B.tcmv_plan_gemm_kernel(pl.handle, "fc2_gemm", 0) == "256x320 persistent + 64x64 slices"
+    assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, "slices behind whole rounds")
+    again = enc.encode(pl, patches)
+    torch.cuda.synchronize()
+    assert torch.equal(hidden, again)
 
 
 def test_attention_too_wide_for_the_pass_over_the_keys():

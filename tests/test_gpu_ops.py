@@ -513,7 +513,7 @@ def test_gemm_bf16_tile_kernels(epi, m, n, k, kernel):
 
 
 @pytest.mark.parametrize("epi,m,n,k,kernel", [
-    (B.EPI_STORE, 12043, 2568, 448, "256x256 persistent + 64x64"), (B.EPI_GELU, 11949, 2568, 384, "256x256 persistent + 128x128"),
+    (B.EPI_STORE, 12043, 2568, 448, "256x256 persistent + 64x64"), (B.EPI_GELU, 22021, 1288, 512, "256x256 persistent + 64x64"),
     (B.EPI_RESID, 9233, 2568, 128, "256x256 persistent + 128x128"), (B.EPI_RESID, 17667, 3840, 128, "256x320 persistent + 64x64"),
     (B.EPI_GATED, 12045, 2568, 576, "256x256 persistent + 64x64")])
 def test_gemm_bf16_whole_rounds_and_the_rest(epi, m, n, k, kernel):
