@@ -83,6 +83,10 @@ int fail_hip(tcmv_ctx* ctx, hipError_t e, const char* what) {
 // tiles per wave (256 rows with 4 waves, 512 with 8); 512-row items stage every K/V tile once per
 // CU instead of twice and are used when rounding the segments up to 512 rows wastes little.
 int attn_bq_bf16(int dh, int heads, const std::vector<int64_t>& seg_len) {
+  // one tiny request: 64-row items whose keys, at most four tiles, are shared by four groups of waves
+  int64_t items64 = 0, longest = 0;
+  for (int64_t n : seg_len) { items64 += (n + 63) / 64; longest = std::max(longest, n); }
+  if (longest <= 256 && items64 * heads <= 256) return 64;
   if (dh > 80) return 128;
   int64_t rows = 0, padded = 0, items256 = 0, items512 = 0;
   for (int64_t n : seg_len) { rows += n; padded += (n + 511) / 512 * 512; items256 += (n + 255) / 256; items512 += (n + 511) / 512; }
@@ -1077,13 +1081,17 @@ int op_attention_run(int dtype, const void* d_qkv, int d, int heads, const OpAtt
     a.q = q; a.k = q + d; a.ldqk = 3 * d; a.v = scratch + L.vt; a.ldv = L.t_vpad;
     a.scale = (float)(1.4426950408889634 / std::sqrt((double)dh));
     a.prescaled = 0;                               // the caller's queries are unscaled
-    uint32_t* kmax = reinterpret_cast<uint32_t*>(scratch + L.kmax);
-    e = launch_fill_zero(kmax, L.kmax_bytes, s);
-    if (e != hipSuccess) return TCMV_E_HIP;
-    e = launch_knorm(q + d, 3 * d, L.T, heads, dh, reinterpret_cast<const int32_t*>(idx + L.rseg), kmax, s);
-    if (e != hipSuccess) return TCMV_E_HIP;
-    a.kmax2 = kmax;
-    a.any_left = kmax + L.n_seg * (size_t)heads * kKmaxStride;
+    if (L.bq == 64) {                              // these items do without key norms
+      if (!knorm_available(heads, dh)) return TCMV_E_HIP;
+    } else {
+      uint32_t* kmax = reinterpret_cast<uint32_t*>(scratch + L.kmax);
+      e = launch_fill_zero(kmax, L.kmax_bytes, s);
+      if (e != hipSuccess) return TCMV_E_HIP;
+      e = launch_knorm(q + d, 3 * d, L.T, heads, dh, reinterpret_cast<const int32_t*>(idx + L.rseg), kmax, s);
+      if (e != hipSuccess) return TCMV_E_HIP;
+      a.kmax2 = kmax;
+      a.any_left = kmax + L.n_seg * (size_t)heads * kKmaxStride;
+    }
     e = launch_attn_bf16(a, s);
   } else {
     const float* q = reinterpret_cast<const float*>(d_qkv);

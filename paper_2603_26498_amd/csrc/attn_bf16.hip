@@ -98,13 +98,18 @@ struct AttnCfg {
 // the FAST copy processes the workgroups whose scores are provably small without any softmax
 // reference and returns at once for the others, the other copy does the opposite.  Two
 // kernels instead of one branch keep the register allocation of each loop to itself.
-template <int DH, int NT, int NWV, bool PRESC, bool FAST>
-__global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a) {
+// KG: groups of NWV waves that share the query rows of a workgroup and split its keys.  A small request has fewer work
+// items than CUs, so a wave is alone on its SIMD and waits for its own chain (fragments, scores, maximum, exponentials,
+// PV product) in every block of keys; KG groups with a ring of NST stages each halve or quarter that chain.  Their
+// statistics and outputs meet in LDS at the end.
+template <int DH, int NT, int NWV, bool PRESC, bool FAST, int KG = 1, int NST = kStages>
+__global__ __launch_bounds__(NWV * KG * 64, KG > 1 ? 1 : 8 / NWV) void attn_bf16_kernel(AttnArgs a) {
   using C = AttnCfg<DH>;
-  constexpr int NTHREADS = NWV * 64;
+  static_assert(KG == 1 || !FAST, "key groups merge softmax statistics");
+  constexpr int NTHREADS = NWV * 64;               // of a key group
   constexpr int NLD = (C::NW + NWV - 1) / NWV;     // tile loads per wave
   constexpr int WQ = 32 * NT;             // query rows per wave
-  __shared__ __attribute__((aligned(16))) uint8_t smem[kStages * C::STAGE];
+  __shared__ __attribute__((aligned(16))) uint8_t smem_all[KG * NST * C::STAGE];
 
   // the key-norm block of the next layer is cleared by the first workgroup of the first kernel of this launch
   if (FAST && blockIdx.x == 0 && a.kmax_clear)
@@ -114,13 +119,23 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
   const int p = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
   if (p >= total) return;
   const int head = p / a.n_work;
-  const AttnWork w = a.work[p - head * a.n_work];
+  AttnWork w = a.work[p - head * a.n_work];
 
   // the reference-tracking copy runs after the other one (same stream), which has recorded whether it
   // left any workgroup behind
   if (!FAST && a.kmax2 && a.any_left && *a.any_left == 0) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int group = KG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / NTHREADS) : 0;
+  const int tid = (int)threadIdx.x - group * NTHREADS, lane = tid & 63, wave = tid >> 6;
   __builtin_assume(tid >= 0 && tid < NTHREADS);
+  uint8_t* const smem = smem_all + group * NST * C::STAGE;
+  int n_rounds = 0;                                // KG > 1: tiles of the first group, which has the most
+  if (KG > 1) {                                    // this group's share of the keys, in whole tiles; may be empty
+    n_rounds = ((w.seg_len + BKV - 1) / BKV + KG - 1) / KG;
+    const int key0 = min(group * n_rounds * BKV, w.seg_len);
+    w.seg_start += key0;
+    w.v0 += key0;
+    w.seg_len = min(w.seg_len - key0, n_rounds * BKV);
+  }
   const int lr = lane & 31, lg = lane >> 5;
   const uint16_t* Q = reinterpret_cast<const uint16_t*>(a.q);
   const uint16_t* K = reinterpret_cast<const uint16_t*>(a.k);
@@ -128,7 +143,7 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
 
   // padding rows of the V^T tiles: ones row (denominator) then zeros
   if (C::DHP > DH) {
-    for (int i = tid; i < kStages * (C::DHP - DH) * (BKV / 2); i += NTHREADS) {
+    for (int i = tid; i < NST * (C::DHP - DH) * (BKV / 2); i += NTHREADS) {
       const int buf = i / ((C::DHP - DH) * (BKV / 2));
       const int rem = i - buf * ((C::DHP - DH) * (BKV / 2));
       const int row = DH + rem / (BKV / 2), c2 = rem % (BKV / 2);
@@ -225,6 +240,17 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) { m_run[nt] = -INFINITY; l_run[nt] = 0.f; }
   const float cs = a.scale;   // softmax scale * log2(e)
+  // One query tile per wave and scaled queries: the score product starts from minus the softmax reference instead of zero,
+  // so a score leaves the MFMA as the exponent itself and no subtraction per element follows.  The matrix unit wants its
+  // start values in a register each: 16 that hold the same number and are rewritten only when the reference moves (32 for
+  // two query tiles would not fit).  63 -> 45 vector instructions for 32 keys: 28 x 577 tokens, 16 heads of 64, 69.0 -> 63.4 us;
+  // 5 x 729, heads of 80, 26.5 -> 24.4; 1120 tokens 19.9 -> 18.6.
+  // `limit`: the largest exponent that does not move the reference (-inf until a block has set it).
+  constexpr bool NEGM = PRESC && !FAST && NT == 1;
+  f32x16 negm;
+  float limit = -INFINITY;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) negm[v] = 0.f;
 
   const int n_tiles = (w.seg_len + BKV - 1) / BKV;
   const bool ragged = (w.seg_len % BKV) != 0;
@@ -243,7 +269,7 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) s[nt][v] = 0.f;
+      for (int v = 0; v < 16; ++v) s[nt][v] = NEGM ? negm[v] : 0.f;
 #pragma unroll
     for (int ks = 0; ks < C::KS; ++ks)
 #pragma unroll
@@ -296,6 +322,29 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[mt][nt][v] *= alpha[nt];
   };
+  // The same for NEGM: only the block maximum; the reference moves (rarely) in rebase, out of line, which takes along the
+  // block that was scored against the old one.
+  auto block_max = [&](const f32x16& s) -> float {
+    float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
+#pragma unroll
+    for (int v = 3; v + 1 < 16; v += 2) mx = fmaxf(fmaxf(mx, s[v]), s[v + 1]);
+    mx = fmaxf(mx, s[15]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+  };
+  auto rebase = [&](f32x16& s, float mx) __attribute__((always_inline)) {
+    const bool move = mx > limit;
+    const float d = move ? mx : 0.f;
+    const float f = move && limit == kLazy ? __builtin_amdgcn_exp2f(-d) : 1.f;     // nothing accumulated before the first one
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { s[v] -= d; negm[v] -= d; }
+#pragma unroll
+    for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[mt][0][v] *= f;
+    l_run[0] *= f;
+    limit = move ? kLazy : limit;
+  };
   // One region = one 32-key block of the online softmax, one basic block of code in the
   // unmasked case: the score MFMAs of the NEXT block (fragments already in kf), the
   // exponentials of the CURRENT block, its PV MFMAs, the statistics of the next block and the
@@ -308,7 +357,7 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
                     float (&alpha)[NT]) -> bool {
     float mc[NT], psum[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) { mc[nt] = m_run[nt] * cs; psum[nt] = 0.f; }
+    for (int nt = 0; nt < NT; ++nt) { mc[nt] = KG > 1 && m_run[nt] == -INFINITY ? 0.f : m_run[nt] * cs; psum[nt] = 0.f; }
     // probabilities of keys 16j..16j+15 of the current block, packed as the PV B operand
     auto exp_half = [&](int j, bf16x8 (&pf)[NT]) {
 #pragma unroll
@@ -316,8 +365,9 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
         uint32_t pk[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float a0 = __builtin_amdgcn_exp2f(fmaf(s_cur[nt][8 * j + 2 * e], cs, -mc[nt]));
-          const float a1 = __builtin_amdgcn_exp2f(fmaf(s_cur[nt][8 * j + 2 * e + 1], cs, -mc[nt]));
+          const float x0 = s_cur[nt][8 * j + 2 * e], x1 = s_cur[nt][8 * j + 2 * e + 1];
+          const float a0 = __builtin_amdgcn_exp2f(NEGM ? x0 : fmaf(x0, cs, -mc[nt]));
+          const float a1 = __builtin_amdgcn_exp2f(NEGM ? x1 : fmaf(x1, cs, -mc[nt]));
           if (!C::ONES) psum[nt] += a0 + a1;
           pk[e] = pack_bf16x2(a0, a1);
         }
@@ -352,17 +402,22 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
       if (!C::ONES) l_run[nt] += psum[nt];
     k_frags(sk_pref, kb_pref);
     bool need = false;
+    auto stats = [&]() {
+      if constexpr (NEGM) { alpha[0] = block_max(s_next[0]); need = alpha[0] > limit; }
+      else need = stats_block(s_next, alpha);
+    };
     if constexpr (decltype(masked)::value) {
       if (next_mask) mask_block(s_next, next_key0);
-      if (next_valid) need = stats_block(s_next, alpha);
+      if (next_valid) stats();
     } else {
-      need = stats_block(s_next, alpha);
+      stats();
     }
     if constexpr (decltype(masked)::value) {
       __builtin_amdgcn_iglp_opt(3);
     } else {
       constexpr int n_mfma = C::KS * NT + 2 * C::MT * NT;
-      constexpr int n_valu = 16 * NT * 3 + 8 * NT + 16 * NT + 24;      // fma, exp2, max / pack / statistics and addresses
+      // (fma,) exp2, max / pack / statistics and addresses
+      constexpr int n_valu = NEGM ? 16 + 8 + 8 + (C::ONES ? 0 : 16) + 16 : 16 * NT * 3 + 8 * NT + 16 * NT + 24;
 #pragma unroll
       for (int i = 0; i < n_mfma; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -541,7 +596,7 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
   // LDS ring of three stages.  At the barrier that opens iteration t, tile t+1 has landed (its
   // loads were issued one iteration earlier) and every wave is done with tile t-1, so tile
   // t+2 can be requested into that stage; nothing else synchronises the waves.
-  load_tile(0, 0, ragged && n_tiles == 1);
+  if (KG == 1 || n_tiles > 0) load_tile(0, 0, ragged && n_tiles == 1);
   if (n_tiles > 1) load_tile(1, 1, ragged && n_tiles == 2);
   // tile 0 (the older one) has landed once at most a tile's worth of loads is outstanding; waves
   // issue NW/NWV or NW/NWV+1 loads per tile, so the smaller count is the safe threshold for all
@@ -549,13 +604,14 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
   else wait_tile();
   __syncthreads();
   f32x16 s0[NT], s1[NT];
-  {
+  if (KG == 1 || n_tiles > 0) {
     float alpha[NT];
     k_frags(smem, 0);
     score_block(s0);
     k_frags(smem, 1);
     if (ragged && n_tiles == 1) mask_block(s0, 0);
-    if (!FAST) (void)stats_block(s0, alpha);      // O is still zero: nothing to rescale
+    if constexpr (NEGM) rebase(s0[0], block_max(s0[0]));
+    else if (!FAST) (void)stats_block(s0, alpha);  // O is still zero: nothing to rescale
   }
   int st = 0;                                     // stage of tile t
   // iteration t: block 0 of tile t (scores in s0) and block 1 (scored in the first region);
@@ -563,8 +619,8 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
   // comes from a stale stage and is ignored.
   auto iteration = [&](auto masked, int t) {
     const int j0 = t * BKV;
-    const int st1 = (st + 1 == kStages) ? 0 : st + 1;
-    const int st2 = (st1 + 1 == kStages) ? 0 : st1 + 1;
+    const int st1 = (st + 1 == NST) ? 0 : st + 1;
+    const int st2 = (st1 + 1 == NST) ? 0 : st1 + 1;
     const uint8_t* sv = smem + st * C::STAGE + C::K_BYTES;
     const uint8_t* sk1 = smem + st1 * C::STAGE;
     wait_tile();
@@ -585,9 +641,13 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
     } else {
       float alpha[NT];
       bool need = region(masked, s1, s0, sv, 0, sk1, 0, true, ragged && t + 1 == n_tiles, j0 + 32, alpha);
-      if (__builtin_expect(__any(need), 0)) rescale(alpha);
+      auto moved = [&](f32x16 (&s)[NT]) __attribute__((always_inline)) {
+        if constexpr (NEGM) rebase(s[0], alpha[0]);
+        else rescale(alpha);
+      };
+      if (__builtin_expect(__any(need), 0)) moved(s1);
       need = region(masked, s0, s1, sv, 1, sk1, 1, t + 1 < n_tiles, ragged && t + 2 == n_tiles, j0 + BKV, alpha);
-      if (__builtin_expect(__any(need), 0)) rescale(alpha);
+      if (__builtin_expect(__any(need), 0)) moved(s0);
     }
     st = st1;
   };
@@ -607,6 +667,47 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
     asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]), "+v"(kf[4]));
   }
   for (; t < n_tiles; ++t) iteration(std::true_type{}, t);
+
+  if constexpr (KG > 1) {
+    // groups with fewer tiles keep the barriers of the first; then every group but the first leaves its statistics and
+    // outputs in LDS ([value][lane], so consecutive lanes hit consecutive banks) and the first adds them in group order
+    for (int i = n_tiles; i < n_rounds; ++i) __syncthreads();
+    __syncthreads();
+    if (NEGM) m_run[0] = limit == -INFINITY ? -INFINITY : -negm[0];
+    constexpr int PART = (C::MT * 16 + 2) * NT * 64;
+    static_assert((KG - 1) * NWV * PART * 4 <= KG * NST * C::STAGE, "exchange area");
+    float* part = reinterpret_cast<float*>(smem_all) + lane;
+    if (group > 0) {
+      float* mine = part + ((group - 1) * NWV + wave) * PART;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+        for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) mine[((nt * C::MT + mt) * 16 + v) * 64] = o[mt][nt][v];
+        mine[(NT * C::MT * 16 + 2 * nt) * 64] = m_run[nt];
+        mine[(NT * C::MT * 16 + 2 * nt + 1) * 64] = l_run[nt];
+      }
+    }
+    __syncthreads();
+    if (group > 0) return;
+    for (int g = 0; g < KG - 1; ++g) {
+      const float* other = part + (g * NWV + wave) * PART;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const float mo = other[(NT * C::MT * 16 + 2 * nt) * 64], lo = other[(NT * C::MT * 16 + 2 * nt + 1) * 64];
+        const float mn = fmaxf(m_run[nt], mo);
+        const float f = m_run[nt] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run[nt] - mn) * cs);
+        const float fo = mo == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mo - mn) * cs);
+        m_run[nt] = mn;
+        l_run[nt] = l_run[nt] * f + lo * fo;
+#pragma unroll
+        for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) o[mt][nt][v] = o[mt][nt][v] * f + other[((nt * C::MT + mt) * 16 + v) * 64] * fo;
+      }
+    }
+  }
 
   // ---- normalise and store: lane holds query (lane & 31), head-dim rows 8*(v/4) + 4*lg + v%4
 #pragma unroll
@@ -638,6 +739,26 @@ __global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a
   }
 }
 
+// Small requests without key norms, keys split over groups of waves.  One image of 1120 tokens, 16 heads of 80 (144 items
+// of 128 rows): 24.7 -> 21.4 us a layer; 256 tokens: 9.6 -> 8.7, of which 4.6 pass before the first scores and behind the last.
+// 64-row items of segments of at most 256 keys (a tile of keys for each of four groups, so no ring), otherwise 128-row
+// items as long as every one has a CU of its own: from two on a CU on, the rings of a second group do not fit LDS and
+// the other workgroup covers the waits anyway.
+template <bool PRESC>
+static hipError_t launch_attn_groups(const AttnArgs& a, unsigned grid, hipStream_t s) {
+#define TCMV_ATTN_CASE(D)                                                                                                        \
+  case D:                                                                                                                        \
+    if (a.bq == 64) hipLaunchKernelGGL((attn_bf16_kernel<D, 1, 2, PRESC, false, 4, 1>), dim3(grid), dim3(512), 0, s, a);         \
+    else hipLaunchKernelGGL((attn_bf16_kernel<D, 1, 4, PRESC, false, 2>), dim3(grid), dim3(512), 0, s, a);                       \
+    break;
+  switch (a.dh) {
+    TCMV_ATTN_CASE(32) TCMV_ATTN_CASE(64) TCMV_ATTN_CASE(80) TCMV_ATTN_CASE(96)
+    default: return hipErrorInvalidValue;
+  }
+#undef TCMV_ATTN_CASE
+  return hipGetLastError();
+}
+
 template <bool PRESC, bool FAST>
 static hipError_t launch_attn_t(const AttnArgs& a, unsigned grid, hipStream_t s) {
 #define TCMV_ATTN_CASE(D)                                                                                     \
@@ -663,7 +784,8 @@ hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s) {
   const int64_t total = (int64_t)a.n_work * a.heads;
   if (total > (1 << 30)) return hipErrorInvalidValue;
   if (a.ldqk % 8 || a.ldv % 8 || a.ldo % 4) return hipErrorInvalidValue;
-  if (a.bq != 128 && a.bq != 256 && a.bq != 512) return hipErrorInvalidValue;
+  if (a.bq != 64 && a.bq != 128 && a.bq != 256 && a.bq != 512) return hipErrorInvalidValue;
+  if (a.bq == 64 && a.kmax2) return hipErrorInvalidValue;
   // operands are addressed in bytes, 32 bits
   if ((double)a.t_total * (double)a.ldqk * 2.0 >= 4294967296.0 || (double)a.heads * a.dh * (double)a.ldv * 2.0 >= 4294967296.0) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)(((total + 7) / 8) * 8);
@@ -673,6 +795,8 @@ hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s) {
     const hipError_t e = a.prescaled ? launch_attn_t<true, true>(a, grid, s) : launch_attn_t<false, true>(a, grid, s);
     if (e != hipSuccess) return e;
   }
+  if (a.bq == 64 || (a.bq == 128 && !a.kmax2 && total <= 256))
+    return a.prescaled ? launch_attn_groups<true>(a, grid, s) : launch_attn_groups<false>(a, grid, s);
   return a.prescaled ? launch_attn_t<true, false>(a, grid, s) : launch_attn_t<false, false>(a, grid, s);
 }
 

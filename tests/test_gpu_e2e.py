@@ -249,6 +249,24 @@ def test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(heads, 
     assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, kernel)
 
 
+@pytest.mark.parametrize("dh", [32, 64, 72, 80, 96])
+@pytest.mark.parametrize("spread", [0.36, 1.43])
+@pytest.mark.parametrize("rows,grids", [
+    (64, [(1, 1), (3, 21), (8, 8), (5, 13), (8, 16), (12, 16), (10, 25), (16, 16)]),        # at most one tile of keys for a group
+    (128, [(1, 1), (5, 8), (8, 8), (5, 13), (8, 16), (3, 43), (1, 193), (20, 35)])])        # groups of 0 to 6 tiles, the last one ragged
+def test_attention_of_small_requests_with_the_keys_split_over_groups_of_waves(rows, grids, spread, dh):
+    """One to 700 keys shared by four or two groups of waves, some of them without keys; scores up to about spread^2 (see above)."""
+    heads = 8 if dh == 72 else 4 if dh == 80 else 2          # the width of the model is a multiple of 64
+    desc = workloads.ModelDesc(layers=1, d=heads * dh, heads=heads, mlp=128, patch=14, tpatch=1, merge=1)
+    rng = np.random.default_rng(rows + dh)
+    items = [workloads.Item(workloads.IMAGE, 1, 14 * h, 14 * w, 14 * h, 14 * w, workloads.random_frames(rng, 1, 14 * h, 14 * w)) for h, w in grids]
+    wl = workloads.Workload("key_groups", desc, items, workloads.make_weights(desc, 34, std=spread / desc.d ** 0.5, random_affine=True))
+    ref = oracle.run(wl, workers=4)
+    enc, pl, patches, hidden, out = run_gpu(wl)
+    assert B.tcmv_op_attention_rows(B.TCMV_BF16, pl.cu_seqlens, heads * (enc.dh_lib or dh), heads) == rows and B.tcmv_plan_key_norms(pl.handle, 0) == 0
+    assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, "key groups")
+
+
 def test_qkv_product_in_whole_rounds_and_the_rest():
     """Rotary factors, transposed values and key norms of the rows behind the whole rounds, which a second kernel computes."""
     test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(12, 64, (38, 35), 6, "256x256 persistent + 128x128 k/2", 0.36)
