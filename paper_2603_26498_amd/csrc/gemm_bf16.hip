@@ -1007,7 +1007,8 @@ GemmRoute choose_route(const GemmArgs& a) {
   // by 4.5 % r.m.s.; of 1200 products of 3000 - 102000 rows the best of all measured routes would gain 2.4 % on average, this
   // rule gains 1.5 % and loses more than 2 % on four, 5.5 % at most).  16656 rows: fc2 (1280 x 5120) 242 -> 212 us, with the 272 rows behind
   // the round in slices of k 200; fc1 224 -> 210; 23501 x 1280 x 5120 352 -> 307.
-  if (can_persist && !is_sliced(r.first.kernel)) {
+  // Outside the rows and contractions it is fitted to, products are left as they are (2907 x 8192 x 1024 would lose 4 %).
+  if (can_persist && a.m >= 3000 && a.k >= 1024 && !is_sliced(r.first.kernel)) {
     float best = is_persistent(r.first.kernel) ? rounds_cost(a, kTileKernels[r.first.kernel - GK_P320], a.m) : cost;
     best *= 0.97f;
     const bool persistent = big_tiles >= 400;

@@ -269,7 +269,7 @@ def test_attention_of_small_requests_with_the_keys_split_over_groups_of_waves(ro
 
 def test_qkv_product_in_whole_rounds_and_the_rest():
     """Rotary factors, transposed values and key norms of the rows behind the whole rounds, which a second kernel computes."""
-    test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(12, 64, (38, 35), 6, "256x256 persistent + 128x128 k/2", 0.36)
+    test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(16, 80, (33, 33), 6, "256x320 persistent + 128x160", 0.36)
 
 
 def test_rows_behind_whole_rounds_in_slices_of_k():

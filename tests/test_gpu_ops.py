@@ -513,9 +513,9 @@ def test_gemm_bf16_tile_kernels(epi, m, n, k, kernel):
 
 
 @pytest.mark.parametrize("epi,m,n,k,kernel", [
-    (B.EPI_STORE, 12043, 2568, 448, "256x256 persistent + 64x64"), (B.EPI_GELU, 22021, 1288, 512, "256x256 persistent + 64x64"),
-    (B.EPI_RESID, 9233, 2568, 128, "256x256 persistent + 128x128"), (B.EPI_RESID, 17667, 3840, 128, "256x320 persistent + 64x64"),
-    (B.EPI_GATED, 12045, 2568, 576, "256x256 persistent + 64x64")])
+    (B.EPI_STORE, 14851, 1288, 1024, "256x256 persistent + 256x128"), (B.EPI_GELU, 7688, 2568, 1152, "256x320 persistent + 64x64"),
+    (B.EPI_RESID, 16897, 1288, 1024, "256x320 persistent + 128x128"), (B.EPI_RESID, 20226, 1032, 1024, "256x256 persistent + 256x160"),
+    (B.EPI_GATED, 10246, 1928, 1152, "256x256 persistent + 128x160")])
 def test_gemm_bf16_whole_rounds_and_the_rest(epi, m, n, k, kernel):
     """Whole rounds of large tiles for the first rows, another kernel for the ragged rest."""
     test_gemm_bf16_tile_kernels(epi, m, n, k, kernel)
