@@ -334,7 +334,9 @@ __global__ __launch_bounds__(NWV * KG * 64, KG > 1 ? 1 : 8 / NWV) void attn_bf16
   };
   auto rebase = [&](f32x16& s, float mx) __attribute__((always_inline)) {
     const bool move = mx > limit;
-    const float d = move ? mx : 0.f;
+    // a whole number: probabilities then differ by powers of two between references, and their rounding to bf16 does not
+    // depend on the reference, i.e. on how the keys were split
+    const float d = move ? __builtin_rintf(mx) : 0.f;
     const float f = move && limit == kLazy ? __builtin_amdgcn_exp2f(-d) : 1.f;     // nothing accumulated before the first one
 #pragma unroll
     for (int v = 0; v < 16; ++v) { s[v] -= d; negm[v] -= d; }
