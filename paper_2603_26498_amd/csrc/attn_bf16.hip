@@ -111,6 +111,10 @@ __global__ __launch_bounds__(NWV * KG * 64, KG > 1 ? 1 : 8 / NWV) void attn_bf16
   constexpr int WQ = 32 * NT;             // query rows per wave
   __shared__ __attribute__((aligned(16))) uint8_t smem_all[KG * NST * C::STAGE];
 
+  if (!FAST && blockIdx.x >= a.item_blocks) {
+    touch_lines(a.touch, blockIdx.x - a.item_blocks, gridDim.x - a.item_blocks, NWV * KG * 64);
+    return;
+  }
   // the key-norm block of the next layer is cleared by the first workgroup of the first kernel of this launch
   if (FAST && blockIdx.x == 0 && a.kmax_clear)
     for (int i = threadIdx.x; i < a.n_clear; i += NTHREADS) a.kmax_clear[i] = 0u;
@@ -747,7 +751,8 @@ __global__ __launch_bounds__(NWV * KG * 64, KG > 1 ? 1 : 8 / NWV) void attn_bf16
 // items as long as every one has a CU of its own: from two on a CU on, the rings of a second group do not fit LDS and
 // the other workgroup covers the waits anyway.
 template <bool PRESC>
-static hipError_t launch_attn_groups(const AttnArgs& a, unsigned grid, hipStream_t s) {
+static hipError_t launch_attn_groups(AttnArgs a, hipStream_t s) {
+  const unsigned grid = a.item_blocks + touch_blocks(a.touch, 512, 256 - (int64_t)a.item_blocks);
 #define TCMV_ATTN_CASE(D)                                                                                                        \
   case D:                                                                                                                        \
     if (a.bq == 64) hipLaunchKernelGGL((attn_bf16_kernel<D, 1, 2, PRESC, false, 4, 1>), dim3(grid), dim3(512), 0, s, a);         \
@@ -762,7 +767,8 @@ static hipError_t launch_attn_groups(const AttnArgs& a, unsigned grid, hipStream
 }
 
 template <bool PRESC, bool FAST>
-static hipError_t launch_attn_t(const AttnArgs& a, unsigned grid, hipStream_t s) {
+static hipError_t launch_attn_t(AttnArgs a, hipStream_t s) {
+  const unsigned grid = a.item_blocks + (FAST ? 0u : touch_blocks(a.touch, a.bq == 512 ? 512 : kThreads4, (a.bq == 512 ? 256 : 512) - (int64_t)a.item_blocks));
 #define TCMV_ATTN_CASE(D)                                                                                     \
   case D:                                                                                                     \
     if (a.bq == 512) hipLaunchKernelGGL((attn_bf16_kernel<D, 2, 8, PRESC, FAST>), dim3(grid), dim3(512), 0, s, a);  \
@@ -781,7 +787,8 @@ static hipError_t launch_attn_t(const AttnArgs& a, unsigned grid, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s) {
+hipError_t launch_attn_bf16(const AttnArgs& args, hipStream_t s) {
+  AttnArgs a = args;
   if (a.n_work == 0 || a.heads == 0) return hipSuccess;
   const int64_t total = (int64_t)a.n_work * a.heads;
   if (total > (1 << 30)) return hipErrorInvalidValue;
@@ -790,16 +797,16 @@ hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t s) {
   if (a.bq == 64 && a.kmax2) return hipErrorInvalidValue;
   // operands are addressed in bytes, 32 bits
   if ((double)a.t_total * (double)a.ldqk * 2.0 >= 4294967296.0 || (double)a.heads * a.dh * (double)a.ldv * 2.0 >= 4294967296.0) return hipErrorInvalidValue;
-  const unsigned grid = (unsigned)(((total + 7) / 8) * 8);
+  a.item_blocks = (unsigned)(((total + 7) / 8) * 8);
   // with key norms both copies visit every work item and each item is processed by exactly one of them;
   // without, only the reference-tracking copy runs
   if (a.kmax2) {
-    const hipError_t e = a.prescaled ? launch_attn_t<true, true>(a, grid, s) : launch_attn_t<false, true>(a, grid, s);
+    const hipError_t e = a.prescaled ? launch_attn_t<true, true>(a, s) : launch_attn_t<false, true>(a, s);
     if (e != hipSuccess) return e;
   }
   if (a.bq == 64 || (a.bq == 128 && !a.kmax2 && total <= 256))
-    return a.prescaled ? launch_attn_groups<true>(a, grid, s) : launch_attn_groups<false>(a, grid, s);
-  return a.prescaled ? launch_attn_t<true, false>(a, grid, s) : launch_attn_t<false, false>(a, grid, s);
+    return a.prescaled ? launch_attn_groups<true>(a, s) : launch_attn_groups<false>(a, s);
+  return a.prescaled ? launch_attn_t<true, false>(a, s) : launch_attn_t<false, false>(a, s);
 }
 
 // Largest squared key norm per (segment, head), the input of the attention kernel's decision

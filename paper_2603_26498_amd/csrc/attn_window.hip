@@ -36,6 +36,7 @@ __global__ __launch_bounds__(128) void attn_window_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t sk[kWinKeys * KSTR];
   __shared__ __attribute__((aligned(16))) uint8_t sv[DHP * 128];
 
+  if (blockIdx.x >= a.item_blocks) { touch_lines(a.touch, blockIdx.x - a.item_blocks, gridDim.x - a.item_blocks, 128); return; }
   const int total = a.n_work * a.heads;
   const int chunk = (total + 7) >> 3;
   const int p = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);   // consecutive p on one XCD
@@ -164,12 +165,14 @@ __global__ __launch_bounds__(128) void attn_window_kernel(AttnArgs a) {
 
 // Every work item must be a whole window of at most 64 tokens (q0 == seg_start, nq == seg_len <= 64) and the
 // queries must already carry the softmax scale; the caller guarantees both.
-hipError_t launch_attn_window_bf16(const AttnArgs& a, hipStream_t s) {
+hipError_t launch_attn_window_bf16(const AttnArgs& args, hipStream_t s) {
+  AttnArgs a = args;
   if (a.n_work == 0 || a.heads == 0) return hipSuccess;
   if (!a.prescaled || a.ldqk % 8 || a.ldv % 8 || a.ldo % 8 || reinterpret_cast<uintptr_t>(a.out) % 16) return hipErrorInvalidValue;
   const int64_t total = (int64_t)a.n_work * a.heads;
   if (total > (1 << 30)) return hipErrorInvalidValue;
-  const unsigned grid = (unsigned)(((total + 7) / 8) * 8);
+  a.item_blocks = (unsigned)(((total + 7) / 8) * 8);
+  const unsigned grid = a.item_blocks + touch_blocks(a.touch, 128, 6 * 256 - (int64_t)a.item_blocks);   // six workgroups fit on a CU
   switch (a.dh) {
     case 32: hipLaunchKernelGGL(attn_window_kernel<32>, dim3(grid), dim3(128), 0, s, a); break;
     case 64: hipLaunchKernelGGL(attn_window_kernel<64>, dim3(grid), dim3(128), 0, s, a); break;

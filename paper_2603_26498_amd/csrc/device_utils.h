@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
+#include "tcmv_internal.h"
 
 namespace tcmv {
 
@@ -56,6 +57,25 @@ __device__ __forceinline__ void static_for_impl(F& f) {
 }
 template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl<0, N>(f); }
+
+// Workgroup `block` of a launch's touching workgroups (a multiple of 8, of nt threads each) reads a word of every line that is
+// its own.  Workgroup ids modulo 8 are XCDs: each takes one contiguous eighth of a matrix, the rows that the product's
+// workgroups on that XCD read (they walk the columns of the output in such eighths).
+__device__ __forceinline__ void touch_lines(const Touch& t, unsigned block, unsigned blocks, unsigned nt) {
+  const uint32_t part = block & 7, stride = (blocks >> 3) * nt;
+  for (int r = 0; r < 4; ++r) {
+    const uint32_t lines = t.bytes[r] >> 7;            // a last line that is not whole stays untouched
+    const uint32_t lo = (uint32_t)((uint64_t)lines * part >> 3), hi = (uint32_t)((uint64_t)lines * (part + 1) >> 3);
+    const char* p = reinterpret_cast<const char*>(t.p[r]);
+    for (uint32_t i = lo + (block >> 3) * nt + threadIdx.x; i < hi; i += kTouchLines * stride) {
+      uint32_t v[kTouchLines];
+#pragma unroll
+      for (int j = 0; j < kTouchLines; ++j) v[j] = *reinterpret_cast<const uint32_t*>(p + (size_t)min(i + j * stride, hi - 1) * 128);
+#pragma unroll
+      for (int j = 0; j < kTouchLines; ++j) asm volatile("" ::"v"(v[j]));
+    }
+  }
+}
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

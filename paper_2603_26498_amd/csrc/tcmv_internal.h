@@ -49,6 +49,22 @@ struct AttnWork {
   int pad_[2];
 };
 
+// Weights that the next products of a small request read: workgroups behind those that compute touch every line of them, so
+// that they come from memory while a launch leaves CUs idle and the products find them in the caches.
+struct Touch { const void* p[4]; uint32_t bytes[4]; };
+// Workgroups of `threads` for it, a multiple of 8 (0: nothing to touch): kTouchLines lines of 128 bytes for a thread.  They
+// occupy CUs like the others, so only the `room` workgroups that the launch leaves free take part, twice that many lines at
+// most; what that does not cover is dropped (3 x 576 tokens, heads of 64, leave 16 CUs: touching all 25 MB from there made
+// the launch 11 us longer).
+constexpr int kTouchLines = 4;
+inline unsigned touch_blocks(Touch& t, unsigned threads, int64_t room) {
+  const uint64_t each = 128ull * threads * kTouchLines;
+  const uint64_t blocks = room > 0 ? (uint64_t)room / 8 * 8 : 0;
+  uint64_t left = 2 * blocks * each, total = 0;
+  for (uint32_t& b : t.bytes) { b = (uint32_t)(b < left ? b : left); left -= b; total += b; }
+  return (unsigned)(((total + each - 1) / each + 7) / 8 * 8 < blocks ? ((total + each - 1) / each + 7) / 8 * 8 : blocks);
+}
+
 enum Epilogue {
   EPI_STORE = 0,   // C = acc + bias                      (bf16 or fp32 by path)
   EPI_GELU = 1,    // C = gelu(acc + bias)
@@ -105,6 +121,7 @@ struct AttnArgs {
   uint32_t* any_left;                            // with kmax2, may be null: zeroed word; set when a workgroup needs the reference-tracking copy
   uint32_t* kmax_clear; int n_clear;             // with kmax2, may be null: n_clear words that the first kernel of the launch zeroes
                                                  // (the key-norm block of the next layer)
+  Touch touch; unsigned item_blocks;             // weights to touch, by the workgroups from item_blocks on (set by the launcher)
 };
 
 struct PreprocArgs {
