@@ -102,8 +102,8 @@ struct AttnCfg {
 // items than CUs, so a wave is alone on its SIMD and waits for its own chain (fragments, scores, maximum, exponentials,
 // PV product) in every block of keys; KG groups with a ring of NST stages each halve or quarter that chain.  Their
 // statistics and outputs meet in LDS at the end.
-template <int DH, int NT, int NWV, bool PRESC, bool FAST, int KG = 1, int NST = kStages>
-__global__ __launch_bounds__(NWV * KG * 64, KG > 1 ? 1 : 8 / NWV) void attn_bf16_kernel(AttnArgs a) {
+template <int DH, int NT, int NWV, bool PRESC, bool FAST, int KG, int NST>
+__device__ __forceinline__ void attention(const AttnArgs& a) {
   using C = AttnCfg<DH>;
   static_assert(KG == 1 || !FAST, "key groups merge softmax statistics");
   constexpr int NTHREADS = NWV * 64;               // of a key group
@@ -745,6 +745,12 @@ __global__ __launch_bounds__(NWV * KG * 64, KG > 1 ? 1 : 8 / NWV) void attn_bf16
   }
 }
 
+template <int DH, int NT, int NWV, bool PRESC, bool FAST>
+__global__ __launch_bounds__(NWV * 64, 8 / NWV) void attn_bf16_kernel(AttnArgs a) { attention<DH, NT, NWV, PRESC, FAST, 1, kStages>(a); }
+
+template <int DH, int NT, int NWV, bool PRESC, bool FAST, int KG, int NST>
+__global__ __launch_bounds__(NWV * KG * 64, 1) void attn_bf16_groups_kernel(AttnArgs a) { attention<DH, NT, NWV, PRESC, FAST, KG, NST>(a); }
+
 // Small requests without key norms, keys split over groups of waves.  One image of 1120 tokens, 16 heads of 80 (144 items
 // of 128 rows): 24.7 -> 21.4 us a layer; 256 tokens: 9.6 -> 8.7, of which 4.6 pass before the first scores and behind the last.
 // 64-row items of segments of at most 256 keys (a tile of keys for each of four groups, so no ring), otherwise 128-row
@@ -755,8 +761,8 @@ static hipError_t launch_attn_groups(AttnArgs a, hipStream_t s) {
   const unsigned grid = a.item_blocks + touch_blocks(a.touch, 512, 256 - (int64_t)a.item_blocks);
 #define TCMV_ATTN_CASE(D)                                                                                                        \
   case D:                                                                                                                        \
-    if (a.bq == 64) hipLaunchKernelGGL((attn_bf16_kernel<D, 1, 2, PRESC, false, 4, 1>), dim3(grid), dim3(512), 0, s, a);         \
-    else hipLaunchKernelGGL((attn_bf16_kernel<D, 1, 4, PRESC, false, 2>), dim3(grid), dim3(512), 0, s, a);                       \
+    if (a.bq == 64) hipLaunchKernelGGL((attn_bf16_groups_kernel<D, 1, 2, PRESC, false, 4, 1>), dim3(grid), dim3(512), 0, s, a);         \
+    else hipLaunchKernelGGL((attn_bf16_groups_kernel<D, 1, 4, PRESC, false, 2, kStages>), dim3(grid), dim3(512), 0, s, a);                       \
     break;
   switch (a.dh) {
     TCMV_ATTN_CASE(32) TCMV_ATTN_CASE(64) TCMV_ATTN_CASE(80) TCMV_ATTN_CASE(96)
