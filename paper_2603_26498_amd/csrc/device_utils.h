@@ -77,10 +77,21 @@ __device__ __forceinline__ void touch_lines(const Touch& t, unsigned block, unsi
   }
 }
 
+// Sum over the 64 lanes, in every lane: the pairs of an exchange with lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2, ^ 1 (from ^ 4 on the
+// lane four further in the row of 16 holds the same value as lane ^ 4), through the vector ALU instead of LDS.
+template <int CTRL>
+__device__ __forceinline__ float add_dpp(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  const auto half = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(half[0]) + __uint_as_float(half[1]);
+  const auto row = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(row[0]) + __uint_as_float(row[1]);
+  v = add_dpp<0x128>(v);                           // row_ror:8
+  v = add_dpp<0x124>(v);                           // row_ror:4
+  v = add_dpp<0x4E>(v);                            // quad_perm [2,3,0,1]
+  return add_dpp<0xB1>(v);                         // quad_perm [1,0,3,2]
 }
 
 }  // namespace tcmv
