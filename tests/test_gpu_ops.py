@@ -397,6 +397,24 @@ def test_gated_epilogue(m, n2, k):
     assert_tokens_close(got, ref, 1e-2, 0.9999, "gated epilogue")
 
 
+def test_gated_epilogue_extreme_gates():
+    """exp(-gate) overflows below -88.7: the output is then 0 (the value itself is below 1e-36), above it is gate * up."""
+    m, n2, k = 64, 512, 64
+    gate = np.tile(np.array([-3e38, -1e4, -100.0, -88.0, -87.0, -30.0, -1.0, 0.0, 1e-30, 1.0, 30.0, 87.0, 100.0, 1e4, 3e30, 1e38], np.float32), n2 // 32)
+    w = np.zeros((n2, k), np.float32)
+    bias = np.empty(n2, np.float32)
+    bias[0::2], bias[1::2] = gate, 0.5
+    c = torch.full((m, n2 // 2), 7.0, dtype=torch.bfloat16, device=DEV)
+    B.tcmv_op_gemm(B.TCMV_BF16, B.EPI_GATED, torch.zeros((m, k), dtype=torch.bfloat16, device=DEV), dev(w, torch.bfloat16), dev(bias), c, m, n2, k)
+    sync()
+    g = gate.astype(np.float64)
+    ref = 0.5 * g / (1.0 + np.exp(np.minimum(-g, 700.0)))
+    got = c.float().cpu().numpy().astype(np.float64)
+    # bf16 keeps 8 significant bits: rounding moves a value by up to 2^-8 of itself; the exponent's rounding (89 * 2^-24) and
+    # the reciprocal are in the 2^-7.99; 2e-36: quotients below the smallest normal number
+    assert np.all(np.abs(got - ref) <= 2.0 ** -7.99 * np.abs(ref) + 2e-36)
+
+
 def test_attention_mixed_norm_bounds_in_one_launch():
     """Some (segment, head, query tile) combinations have provably small scores and are exponentiated without
     a softmax reference, others in the same launch are not: head 0 has large queries, one block of query rows
