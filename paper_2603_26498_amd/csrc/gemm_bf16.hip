@@ -89,8 +89,9 @@ __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[MI][NI], const GemmA
                                               int lane, const TileBounds& tb) {
   constexpr int EPS = kEpStride;
   constexpr int TN = NI * 32;
+  constexpr bool ROPE = EPI == EPI_QKV_ROPE, QKV = EPI == EPI_QKV || ROPE;
   const int lr = lane & 31, lg = lane >> 5;
-  const bool kn = EPI == EPI_QKV && g.kmax2 != nullptr && wcol0 >= g.qcols && wcol0 < g.split;
+  const bool kn = QKV && g.kmax2 != nullptr && wcol0 >= g.qcols && wcol0 < g.split;
   // old values of a group of the output (residual epilogues)
   auto load_old = [&](auto ngc, int nb, int64_t rbase, float4 (&o)[4][2]) {
     constexpr int NGT = decltype(ngc)::value;
@@ -143,7 +144,7 @@ __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[MI][NI], const GemmA
         v[ps][1] = *reinterpret_cast<const float4*>(ep + r * EPS + c8 + 4);
       }
     }
-    if (EPI == EPI_QKV && kn) {
+    if (QKV && kn) {
       // this group's share of the squared key norms: per row, the lanes of the first head of the group and the
       // lanes of the second (a group of 64 columns meets at most two heads of 64 or more columns)
       const int h_first = (nb * 32) / g.kn_dh;
@@ -171,8 +172,24 @@ __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[MI][NI], const GemmA
         }
       }
     }
+    const int rot_col = ROPE ? (col % g.rope_dh) & ~1 : 0;
+    float4 rot[2][2];
 #pragma unroll
     for (int ps = 0; ps < NP; ++ps) {
+      if (ROPE && ps % 2 == 0) {
+        // rotary factors of two passes in one request: asked for pass by pass, each waited behind the stores of the pass
+        // before (windowed encoder, 32768 tokens, QKV 315 -> 310 us; 21 k tokens, heads of 64, 192 -> 181).  All four
+        // passes at once do not fit the registers of the 256x320 kernel (96 spilled).
+        const float* f = g.rope + (size_t)__builtin_amdgcn_readfirstlane((int)rbase) * g.rope_dh;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int r = (ps + j) * RPP + r0;
+          if (FULL || (rbase + r >= tb.row_lo && rbase + r < tb.row_hi)) {
+            const float4* cs = reinterpret_cast<const float4*>(reinterpret_cast<const char*>(f) + (uint32_t)((r * g.rope_dh + rot_col) * 4));
+            rot[j][0] = cs[0]; rot[j][1] = cs[1];
+          }
+        }
+      }
       const int64_t row = rbase + ps * RPP + r0;
       if (!FULL && (row < tb.row_lo || row >= tb.row_hi || !col_ok)) continue;
       if (!BATCH) {
@@ -193,16 +210,14 @@ __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[MI][NI], const GemmA
         for (int j = 0; j < 4; ++j) h[j] = x[2 * j] * __builtin_amdgcn_rcpf(1.0f + __expf(-x[2 * j])) * x[2 * j + 1];
         pk.x = pack_bf16x2(h[0], h[1]); pk.y = pack_bf16x2(h[2], h[3]);
         *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(g.c) + (size_t)row * g.ldc + (col >> 1)) = pk;
-      } else if (EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_QKV) {
-        if (EPI == EPI_QKV && col >= g.split) continue;
-        if (EPI == EPI_QKV && col < g.qcols) {
+      } else if (EPI == EPI_STORE || EPI == EPI_GELU || QKV) {
+        if (QKV && col >= g.split) continue;
+        if (QKV && col < g.qcols) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) x[j] *= g.qscale;
         }
-        if (EPI == EPI_QKV && g.rope) {
-          const int p2 = ((col % g.rope_dh) >> 1) * 2;
-          const float4* cs = reinterpret_cast<const float4*>(g.rope + (size_t)row * g.rope_dh + p2);
-          const float4 c0 = cs[0], c1 = cs[1];
+        if (ROPE) {
+          const float4 c0 = rot[ps % 2][0], c1 = rot[ps % 2][1];
           const float a0 = x[0], a1 = x[1], a2 = x[2], a3 = x[3], a4 = x[4], a5 = x[5], a6 = x[6], a7 = x[7];
           x[0] = a0 * c0.x - a1 * c0.y; x[1] = a0 * c0.y + a1 * c0.x;
           x[2] = a2 * c0.z - a3 * c0.w; x[3] = a2 * c0.w + a3 * c0.z;
@@ -273,8 +288,8 @@ __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[MI][NI], const GemmA
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
     const int64_t rbase = m_base + mi * 32;
-    if (EPI == EPI_QKV && kn && lane < 32) *reinterpret_cast<float4*>(ep + lane * EPS + 64) = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (EPI == EPI_QKV && wcol0 + TN > g.split) {
+    if (QKV && kn && lane < 32) *reinterpret_cast<float4*>(ep + lane * EPS + 64) = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (QKV && wcol0 + TN > g.split) {
       const int64_t row = rbase + lr;
       if (FULL || (row >= tb.row_lo && row < tb.row_hi)) {
         const int vc = g.vcol[row];
@@ -302,7 +317,7 @@ __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[MI][NI], const GemmA
       for (int nb = 0; nb + 2 <= NI; nb += 2) flush(std::integral_constant<int, 2>{}, mi, nb, rbase, none, [] {});
       if (NI & 1) flush(std::integral_constant<int, 1>{}, mi, NI - 1, rbase, none, [] {});
     }
-    if (EPI == EPI_QKV && kn) {
+    if (QKV && kn) {
       // rows of this block -> table.  Lane l < 32 reads the sums of row l (up to four heads per wave tile).
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       const float4 sums = *reinterpret_cast<const float4*>(ep + lr * EPS + 64);
@@ -603,7 +618,7 @@ static hipError_t launch_cfg(const GemmArgs& a, hipStream_t s) {
   } else {
     switch (a.epi) {
       TCMV_GEMM_CASE(EPI_STORE) TCMV_GEMM_CASE(EPI_GELU) TCMV_GEMM_CASE(EPI_RESID)
-      TCMV_GEMM_CASE(EPI_EMBED) TCMV_GEMM_CASE(EPI_QKV) TCMV_GEMM_CASE(EPI_GATED)
+      TCMV_GEMM_CASE(EPI_EMBED) TCMV_GEMM_CASE(EPI_QKV) TCMV_GEMM_CASE(EPI_QKV_ROPE) TCMV_GEMM_CASE(EPI_GATED)
       default: return hipErrorInvalidValue;
     }
   }
@@ -868,7 +883,7 @@ static hipError_t launch_persist(const GemmArgs& a, hipStream_t s) {
   }
   switch (a.epi) {
     TCMV_PGEMM_CASE(EPI_STORE) TCMV_PGEMM_CASE(EPI_GELU) TCMV_PGEMM_CASE(EPI_RESID) TCMV_PGEMM_CASE(EPI_RESID_AHEAD)
-    TCMV_PGEMM_CASE(EPI_EMBED) TCMV_PGEMM_CASE(EPI_QKV) TCMV_PGEMM_CASE(EPI_GATED)
+    TCMV_PGEMM_CASE(EPI_EMBED) TCMV_PGEMM_CASE(EPI_QKV) TCMV_PGEMM_CASE(EPI_QKV_ROPE) TCMV_PGEMM_CASE(EPI_GATED)
     default: return hipErrorInvalidValue;
   }
 #undef TCMV_PGEMM_CASE
@@ -1067,7 +1082,10 @@ const char* gemm_bf16_kernel_name(const GemmArgs& a) {
 
 int gemm_bf16_slices(const GemmArgs& a) { return is_sliced(choose_route(a).first.kernel) ? 4 : 1; }
 
-static hipError_t launch_part(GemmKernel gk, const GemmArgs& a, hipStream_t s) {
+static hipError_t launch_part(GemmKernel gk, const GemmArgs& args, hipStream_t s) {
+  GemmArgs a = args;
+  // a kernel of its own: with the rotation the others keep fewer values in registers (QKV of 4096 tokens 52.3 -> 51.0 us)
+  if (a.epi == EPI_QKV && a.rope) a.epi = EPI_QKV_ROPE;
   if (is_persistent(gk) && a.epi == EPI_RESID && (double)a.m * (double)a.n * 4.0 > 400e6) {
     GemmArgs g = a;                                 // an output larger than the last-level cache: see wave_epilogue
     g.epi = EPI_RESID_AHEAD;

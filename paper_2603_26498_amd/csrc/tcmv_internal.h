@@ -73,7 +73,8 @@ enum Epilogue {
   EPI_QKV = 4,     // columns < split: C ; columns >= split: transposed-V buffer
   EPI_GATED = 5,   // columns come in (gate, up) pairs: C[:, j] = silu(gate_j) * up_j   (C has n/2 columns)
   EPI_PARTIAL = 6, // internal: raw fp32 sums of one slice of k into partial[slice][m][n] (see GemmArgs::partial)
-  EPI_RESID_AHEAD = 7  // internal: EPI_RESID for outputs too large to stay cached; old values requested one group ahead
+  EPI_RESID_AHEAD = 7, // internal: EPI_RESID for outputs too large to stay cached; old values requested one group ahead
+  EPI_QKV_ROPE = 8     // internal: EPI_QKV with rotary positions
 };
 
 struct GemmArgs {
