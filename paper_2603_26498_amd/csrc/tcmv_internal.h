@@ -91,6 +91,7 @@ struct GemmArgs {
   // EPI_QKV with rotary positions: rope[row][p] = (cos, sin) of pair p of a head, p < rope_dh/2;
   // applied to the columns below split (q and k)
   const float* rope; int rope_dh;
+  uint32_t rope_inv;                             // 2^32 / rope_dh rounded up, set by the launcher
   // EPI_QKV: columns below qcols (the queries) are multiplied by qscale before rounding (0 columns = off)
   int qcols; float qscale;
   // EPI_QKV, optional (see gemm_bf16_can_fuse_key_norms): kmax2[row_seg[r]][h] = max(.., 1.008 * |k row r, head h|^2)
