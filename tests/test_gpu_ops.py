@@ -415,6 +415,19 @@ def test_gated_epilogue_extreme_gates():
     assert np.all(np.abs(got - ref) <= 2.0 ** -7.99 * np.abs(ref) + 2e-36)
 
 
+def test_gelu_epilogue_far_from_zero():
+    """Beyond the range of the fit the lower tail has to go on falling: 0 for negative values, the value itself for others."""
+    m, n, k = 64, 512, 64
+    x = np.tile(np.array([-3e38, -1e30, -1e10, -1e4, -300.0, -50.0, -20.0, -9.0, 6.0, 9.0, 20.0, 300.0, 1e4, 1e10, 1e30, 3e38], np.float32), n // 16)
+    c = torch.full((m, n), 7.0, dtype=torch.bfloat16, device=DEV)
+    B.tcmv_op_gemm(B.TCMV_BF16, B.EPI_GELU, torch.zeros((m, k), dtype=torch.bfloat16, device=DEV),
+                   dev(np.zeros((n, k), np.float32), torch.bfloat16), dev(x), c, m, n, k)
+    sync()
+    got = c.float().cpu().numpy()
+    assert np.array_equal(got[:, x > 0], np.broadcast_to(_bf16_round(x[x > 0]), (m, n // 2)))
+    assert np.abs(got[:, x < 0]).max() <= 1e-17          # 9 * Phi(-9) = 1e-18
+
+
 def test_attention_mixed_norm_bounds_in_one_launch():
     """Some (segment, head, query tile) combinations have provably small scores and are exponentiated without
     a softmax reference, others in the same launch are not: head 0 has large queries, one block of query rows
