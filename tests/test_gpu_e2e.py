@@ -267,6 +267,27 @@ def test_attention_of_small_requests_with_the_keys_split_over_groups_of_waves(ro
     assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, "key groups")
 
 
+@pytest.mark.parametrize("grid,n,heads,rows", [((16, 16), 1, 4, 64), ((20, 35), 1, 4, 128), ((24, 24), 16, 8, 128)])
+@pytest.mark.parametrize("border", [0.3, 0.8])
+def test_softmax_reference_moves_between_keys(grid, n, heads, rows, border):
+    """Pictures whose lower part is white under a black one: two kinds of tokens, whose scores differ by far more than 2^8
+    in some heads, so the reference that scores start from moves when the first white keys arrive (or must not, where the
+    black ones score higher).  The tokens of a kind are equal, so a rounded score moves all their probabilities alike and
+    the outputs stay a mixture of two values: the scores (up to 17, 4 to 32 apart) may be larger than in the tests above."""
+    h, w = grid
+    desc = workloads.ModelDesc(layers=1, d=heads * 80, heads=heads, mlp=128, patch=14, tpatch=1, merge=1)
+    items = []
+    for _ in range(n):
+        f = np.zeros((1, 14 * h, 14 * w, 3), np.uint8)
+        f[:, 14 * int(h * border):] = 255
+        items.append(workloads.Item(workloads.IMAGE, 1, 14 * h, 14 * w, 14 * h, 14 * w, f))
+    wl = workloads.Workload("two_kinds", desc, items, workloads.make_weights(desc, 36, std=2.5 / desc.d ** 0.5, random_affine=True))
+    ref = oracle.run(wl, workers=4)
+    enc, pl, patches, hidden, out = run_gpu(wl)
+    assert B.tcmv_op_attention_rows(B.TCMV_BF16, pl.cu_seqlens, heads * 80, heads) == rows and B.tcmv_plan_key_norms(pl.handle, 0) == 0
+    assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, "two kinds of tokens")
+
+
 def test_qkv_product_in_whole_rounds_and_the_rest():
     """Rotary factors, transposed values and key norms of the rows behind the whole rounds, which a second kernel computes."""
     test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(16, 80, (33, 33), 6, "256x320 persistent + 128x160", 0.36)
