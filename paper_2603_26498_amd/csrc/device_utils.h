@@ -48,6 +48,23 @@ __device__ __forceinline__ float gelu_bf16(float x) {
   return fmaf(-fabsf(x), tail, fmaxf(x, 0.0f));
 }
 
+// silu(x) = x / (1 + exp(-x)) of four values, with the bits of the division.  The compiler's division (12 instructions with
+// its scaling and special cases) is most of a gated product's write-out: the quotient by the hardware's reciprocal (1 ulp)
+// instead, put right by its own remainder.  Over all 2^32 arguments that gives the division's bits wherever |x| <= 87.3
+// (without the remainder 2.4 % of them are one step off); beyond, the denominator's reciprocal is subnormal or the
+// remainder not a number, and such a lane divides.
+__device__ __forceinline__ void silu4(const float (&x)[4], float (&y)[4]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float d = 1.0f + __expf(-x[j]), r = __builtin_amdgcn_rcpf(d), q = x[j] * r;
+    y[j] = fmaf(-fmaf(d, q, -x[j]), r, q);           // this sign keeps that of a zero
+  }
+  if (__builtin_expect(fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))) > 87.0f, 0)) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) y[j] = x[j] / (1.0f + __expf(-x[j]));
+  }
+}
+
 // compile-time loop: f(std::integral_constant<int, 0>) ... f(<N-1>)
 template <int I, int N, class F>
 __device__ __forceinline__ void static_for_impl(F& f) {

@@ -410,9 +410,64 @@ def test_gated_epilogue_extreme_gates():
     g = gate.astype(np.float64)
     ref = 0.5 * g / (1.0 + np.exp(np.minimum(-g, 700.0)))
     got = c.float().cpu().numpy().astype(np.float64)
-    # bf16 keeps 8 significant bits: rounding moves a value by up to 2^-8 of itself; the exponent's rounding (89 * 2^-24) and
-    # the reciprocal are in the 2^-7.99; 2e-36: quotients below the smallest normal number
+    # bf16 keeps 8 significant bits: rounding moves a value by up to 2^-8 of itself; the exponent's rounding (89 * 2^-24) is
+    # in the 2^-7.99; 2e-36: exp(-gate) has overflowed
     assert np.all(np.abs(got - ref) <= 2.0 ** -7.99 * np.abs(ref) + 2e-36)
+
+
+def _gates_next_to_bf16_ties():
+    """Gates 6 .. 17 whose quotient gate / (1 + exp(-gate)), rounded to fp32, is half way between two bf16 values or one fp32
+    step beside, where one step more or less changes the bf16.  The denominator is known for certain: 1 + exp(-gate) is
+    a whole number of steps of 2^-23 above 1, and gates whose exp(-gate) comes within a tenth of a step of where that
+    number changes are left out (exp is off by less than 1e-6 of itself, 0.02 steps at 6)."""
+    # bf16 values are 1/32 apart between 4 and 8, 1/16 up to 16, then 1/8
+    ties = np.concatenate([np.arange(6 * 64 + 1, 8 * 64, 2) / 64, np.arange(8 * 32 + 1, 16 * 32, 2) / 32, np.arange(16 * 16 + 1, 17 * 16, 2) / 16])
+    gates = []
+    for t in ties.astype(np.float32):
+        for q in (np.nextafter(t, np.float32(0)), t, np.nextafter(t, np.float32(99))):
+            x = float(q)
+            for _ in range(8):
+                x = float(q) * (1.0 + np.exp(-x))
+            x = np.float32(x)
+            for x in (np.nextafter(x, np.float32(0)), x, np.nextafter(x, np.float32(99))):
+                steps = np.exp(-float(x)) * 2.0 ** 23
+                if x / np.float32(1.0 + np.rint(steps) * 2.0 ** -23) == q and abs(steps % 1.0 - 0.5) > 0.1:
+                    gates.append(x)
+                    break
+    return np.array(gates, np.float32)
+
+
+def _gated_of(gate, up):
+    """silu(gate) * up through the operator: one output column for each pair, the product itself is zero."""
+    n = len(gate)
+    bias = np.stack([gate, np.broadcast_to(np.float32(up), gate.shape)], 1).reshape(-1).astype(np.float32)
+    c = torch.full((64, n), 7.0, dtype=torch.bfloat16, device=DEV)
+    B.tcmv_op_gemm(B.TCMV_BF16, B.EPI_GATED, torch.zeros((64, 64), dtype=torch.bfloat16, device=DEV),
+                   torch.zeros((2 * n, 64), dtype=torch.bfloat16, device=DEV), dev(bias), c, 64, 2 * n, 64)
+    sync()
+    got = c.float().cpu().numpy()
+    assert (got == got[0]).all()
+    return got[0]
+
+
+def test_gated_epilogue_quotient_is_correctly_rounded():
+    """The quotient of the gate has the fp32 rounding of a division: one step off and the bf16 beside is stored."""
+    gate = _gates_next_to_bf16_ties()
+    gate = gate[: len(gate) // 4 * 4]
+    assert len(gate) > 400
+    d = (1.0 + np.rint(np.exp(-gate.astype(np.float64)) * 2.0 ** 23) * 2.0 ** -23).astype(np.float32)
+    got = _gated_of(gate, 1.0)
+    wrong = np.nonzero(got != _bf16_round(gate / d))[0]
+    assert len(wrong) == 0, (len(wrong), len(gate), gate[wrong[:8]], got[wrong[:8]])
+
+
+def test_gated_epilogue_denominators_whose_reciprocal_is_subnormal():
+    """Gates of -87.4 to -88.7: 1 + exp(-gate) is above 2^126, the quotient (2.7e-37 and more) is an ordinary number and
+    a large factor brings it back.  exp of such an argument is off by 2^-17 of itself at most, the bf16 by 2^-9."""
+    gate = np.linspace(-88.7, -87.0, 256).astype(np.float32)
+    got = _gated_of(gate, 2.0 ** 110).astype(np.float64)
+    ref = gate.astype(np.float64) / (1.0 + np.exp(-gate.astype(np.float64))) * 2.0 ** 110
+    assert np.all(np.abs(got - ref) <= (2.0 ** -8 + 2.0 ** -15) * np.abs(ref))
 
 
 def test_gelu_epilogue_far_from_zero():
