@@ -267,6 +267,28 @@ def test_attention_of_small_requests_with_the_keys_split_over_groups_of_waves(ro
     assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, "key groups")
 
 
+@pytest.mark.parametrize("dh", [32, 64, 80, 96])
+@pytest.mark.parametrize("rows,grids", [
+    (64, [(1, 1), (1, 5), (5, 8), (8, 8), (16, 16)]), (128, [(1, 1), (1, 5), (8, 16), (20, 35)]), (128, [(24, 24)] * 28 + [(1, 1)])])
+def test_attention_over_equal_keys_gives_their_value(rows, grids, dh):
+    """Pictures of one colour: all keys of a segment score alike, so every probability is 1 against the largest score (to
+    1e-6, which bf16 rounds away) and the output is the value, whatever the queries and keys are: bit for bit what the
+    model with zero queries and keys computes.  One key alone is the smallest case."""
+    heads = 4 if dh == 80 else 8 if len(grids) > 8 else 2
+    desc = workloads.ModelDesc(layers=1, d=heads * dh, heads=heads, mlp=128, patch=14, tpatch=1, merge=1)
+    items = [workloads.Item(workloads.IMAGE, 1, 14 * h, 14 * w, 14 * h, 14 * w, np.full((1, 14 * h, 14 * w, 3), 37 + 29 * i % 200, np.uint8))
+             for i, (h, w) in enumerate(grids)]
+    res = []
+    for qk in (1, 0):
+        w = workloads.make_weights(desc, 38, std=1.43 / desc.d ** 0.5, random_affine=True)
+        w["l0.w_qkv"][:2 * desc.d] *= qk
+        w["l0.b_qkv"][:2 * desc.d] *= qk
+        enc, pl, patches, hidden, out = run_gpu(workloads.Workload("equal_keys", desc, items, w))
+        assert B.tcmv_op_attention_rows(B.TCMV_BF16, pl.cu_seqlens, desc.d, heads) == rows and B.tcmv_plan_key_norms(pl.handle, 0) == 0
+        res.append(hidden)
+    assert torch.equal(*res)
+
+
 @pytest.mark.parametrize("grid,n,heads,rows", [((16, 16), 1, 4, 64), ((20, 35), 1, 4, 128), ((24, 24), 16, 8, 128)])
 @pytest.mark.parametrize("border", [0.3, 0.8])
 def test_softmax_reference_moves_between_keys(grid, n, heads, rows, border):
