@@ -618,8 +618,31 @@ __device__ __forceinline__ void attention(const AttnArgs& a) {
     score_block(s0);
     k_frags(smem, 1);
     if (ragged && n_tiles == 1) mask_block(s0, 0);
-    if constexpr (NEGM) rebase(s0[0], block_max(s0[0]));
-    else if (!FAST) (void)stats_block(s0, alpha);  // O is still zero: nothing to rescale
+    if (KG == 1 || group == 0) {
+      if constexpr (NEGM) rebase(s0[0], block_max(s0[0]));
+      else if (!FAST) (void)stats_block(s0, alpha);  // O is still zero: nothing to rescale
+    }
+  }
+  if constexpr (KG > 1) {
+    // All groups start from the reference that the first keys of the segment set, as a kernel without groups does: the
+    // probabilities then round to bf16 alike however the keys are split, and a request alone gives what it gives in a batch
+    // (with a reference for each group, tokens of a two-layer model differed by 2.0e-3 of their largest value).
+    static_assert(NT == 1, "one query tile per wave");
+    __shared__ float first_ref[NWV * 32];
+    if (group == 0 && lane < 32) first_ref[wave * 32 + lane] = !NEGM ? m_run[0] : limit == -INFINITY ? -INFINITY : -negm[0];
+    __syncthreads();
+    if (group > 0 && n_tiles > 0) {
+      const float ref = first_ref[wave * 32 + lr];
+      if constexpr (NEGM) {
+        rebase(s0[0], ref);
+        const float mx = block_max(s0[0]);
+        if (__any(mx > limit)) rebase(s0[0], mx);
+      } else {
+        float alpha[NT];
+        m_run[0] = ref;
+        (void)stats_block(s0, alpha);
+      }
+    }
   }
   int st = 0;                                     // stage of tile t
   // iteration t: block 0 of tile t (scores in s0) and block 1 (scored in the first region);
