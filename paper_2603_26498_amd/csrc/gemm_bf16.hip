@@ -944,15 +944,19 @@ float norm_cost(const GemmArgs& a, const TileKernel& t, int64_t m) {
 
 // Estimate for a persistent kernel over whole rounds of tiles, where tile_cost falls short (the chip clocks lower when every
 // CU computes): microseconds a round, by k-tiles and by what the write-out does, and for the last, partly filled round.
-// Fitted to 2400 products of 3000 - 102000 rows.
-struct RoundCost { float base, full_k, part_k, part_k_fill, gelu, resid, qkv, gated; };
-constexpr RoundCost kRoundCosts[] = {{6.1f, 2.13f, 1.01f, 0.97f, 6.9f, 18.5f, 6.3f, 5.3f}, {3.5f, 1.95f, 0.98f, 0.93f, 1.2f, 15.6f, 1.2f, 0.f}};
+// Products that accumulate are narrow (a model's width) and read more of A from memory for a tile: they have constants of
+// their own, fitted to 2400 products of 3000 - 102000 rows (off by 6 and 9 % r.m.s.); those of the others are least squares
+// over 396 products each of 2500 - 102000 rows, n 1024 - 8192, k 1024 - 5120, weights from memory (3.8 and 3.6 %).
+struct RoundCost { float base, full_k, part_k, part_k_fill, resid, store, gelu, qkv, gated; };
+constexpr RoundCost kRoundCosts[2][2] = {                          // 256x320, 256x256; accumulating, the others
+    {{6.1f, 2.13f, 1.01f, 0.97f, 18.5f}, {5.2f, 1.97f, 1.05f, 0.97f, 0.f, 5.5f, 9.0f, 8.9f, 6.2f}},
+    {{3.5f, 1.95f, 0.98f, 0.93f, 15.6f}, {4.7f, 1.60f, 0.83f, 0.77f, 0.f, 4.3f, 7.2f, 7.3f, 4.6f}}};
 
 float rounds_cost(const GemmArgs& a, const TileKernel& t, int64_t m) {
-  const RoundCost& c = kRoundCosts[t.kernel == GK_P320 ? 0 : 1];
+  const RoundCost& c = kRoundCosts[t.kernel == GK_P320 ? 0 : 1][a.epi == EPI_RESID ? 0 : 1];
   const int64_t tiles = ((m + t.bm - 1) / t.bm) * ((a.n + t.bn - 1) / t.bn);
   const float full = (float)(tiles / 256), fill = (float)(tiles % 256) / 256.f, part = fill > 0.f ? 1.f : 0.f, nk = (float)(a.k / 64);
-  const float out = a.epi == EPI_RESID ? c.resid : a.epi == EPI_QKV ? c.qkv : a.epi == EPI_GATED ? c.gated : c.gelu;
+  const float out = a.epi == EPI_RESID ? c.resid : a.epi == EPI_QKV ? c.qkv : a.epi == EPI_GATED ? c.gated : a.epi == EPI_STORE ? c.store : c.gelu;
   return c.base + nk * (full * c.full_k + part * (c.part_k + fill * c.part_k_fill)) + (full + 0.7f * part) * out + norm_cost(a, t, m);
 }
 
@@ -1024,14 +1028,17 @@ GemmRoute choose_route(const GemmArgs& a) {
   }
   // Products with at least one whole round of large tiles: a last round that is nearly empty takes about half as long as a
   // full one, more than the rows in it take as a product of their own.  Both persistent kernels, whole or cut behind their
-  // whole rounds, against what was chosen so far; cut where that is estimated to win by 3 % and 3 us (the estimates are off
-  // by 4.5 % r.m.s.; of 1200 products of 3000 - 102000 rows the best of all measured routes would gain 2.4 % on average, this
-  // rule gains 1.5 % and loses more than 2 % on four, 5.5 % at most).  16656 rows: fc2 (1280 x 5120) 242 -> 212 us, with the 272 rows behind
-  // the round in slices of k 200; fc1 224 -> 210; 23501 x 1280 x 5120 352 -> 307.
-  // Outside the rows and contractions it is fitted to, products are left as they are (2907 x 8192 x 1024 would lose 4 %).
-  if (can_persist && a.m >= 3000 && a.k >= 1024 && !is_sliced(r.first.kernel)) {
+  // whole rounds, against what was chosen so far; cut where that is estimated to win by 1 % and 3 us.  16656 rows: fc2 (1280 x
+  // 5120) 242 -> 212 us, with the 272 rows behind the round in slices of k 200; fc1 224 -> 210; 23501 x 1280 x 5120 352 -> 307.
+  // Of 2065 products of 3000 - 102000 rows measured both ways the better one would gain 7.2 % on average; this rule gains 6.9 %
+  // and loses more than 2 % on 19, 5.3 % at most.
+  // Left as they are: products outside the rows, contractions and widths the estimate is fitted to (2907 x 8192 x 1024 would
+  // lose 4 %, 70138 x 2048 x 2048 into an accumulated output 10 %), and accumulating products over a short contraction whose
+  // rest is half a round or more (21910 x 1280 x 1280, 8854 rows behind one round: 94 us whole, 101 cut).
+  const bool short_sums = a.epi == EPI_RESID && a.k < 3072;
+  if (can_persist && a.m >= 3000 && a.k >= 1024 && !(a.epi == EPI_RESID && a.n >= 2048) && !is_sliced(r.first.kernel)) {
     float best = is_persistent(r.first.kernel) ? rounds_cost(a, kTileKernels[r.first.kernel - GK_P320], a.m) : cost;
-    best *= 0.97f;
+    best *= 0.99f;
     const bool persistent = big_tiles >= 400;
     for (int i = 0; i < 2; ++i) {
       const TileKernel& t = kTileKernels[i];
@@ -1041,11 +1048,11 @@ GemmRoute choose_route(const GemmArgs& a) {
         if (c < best) { best = c; r.first = part(t); r.rows = a.m; }
       }
       const int64_t rows = whole * 256 / tiles_n * 256;
-      if (rows <= 0 || rows >= a.m) continue;
+      if (rows <= 0 || rows >= a.m || (short_sums && (float)(a.m - rows) * (float)a.n > 0.48f * 256.f * (float)(t.bm * t.bn))) continue;
       float c_rest = 0.f;
       const TileKernel* rest = cheapest_tile(a, a.m - rows, true, &c_rest);
       if (is_persistent(rest->kernel)) c_rest = rounds_cost(a, *rest, a.m - rows);
-      else if (a.epi == EPI_GELU || a.epi == EPI_QKV) c_rest *= rest->kernel == GK_T64 ? 1.1f : 1.25f;   // what tile_cost leaves out
+      else if (a.epi == EPI_GELU || a.epi == EPI_QKV) c_rest *= rest->kernel == GK_T64 ? 1.f : 1.25f;    // what tile_cost leaves out
       GemmPart tail = part(*rest);
       if (a.rest_partial && 4 * (a.m - rows) * a.n <= a.rest_floats) consider_slices(a, a.m - rows, false, &c_rest, &tail);
       const float c = rounds_cost(a, t, rows) + c_rest + 3.f;

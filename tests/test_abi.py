@@ -262,6 +262,20 @@ def test_kernels_of_products_that_an_estimate_got_wrong(epi, m, n, k, kernel):
     assert B.tcmv_op_gemm_kernel(epi, m, n, k) == kernel
 
 
+# products that lose time when they are cut behind their whole rounds, although an earlier estimate cut them (whole and cut,
+# microseconds: 23766 x 1152 x 1280 95.5 / 101.5, 32529 x 1024 x 1024 92 / 100, 13186 x 3584 x 5120 376 / 423, 8807 rows 255 / 280,
+# 12877 x 5120 x 5120 525 / 544, 70138 x 2048 x 2048 641 / 713, 14374 rows 136 / 153; 21910 x 1280 x 1280 loses behind
+# 256x256 tiles, 93.9 / 101.3, and gains behind 256x320 ones)
+@pytest.mark.parametrize("epi,m,n,k,kernel", [
+    (B.EPI_RESID, 23766, 1152, 1280, "256x256 persistent"), (B.EPI_RESID, 26938, 1152, 1280, "256x320 persistent"),
+    (B.EPI_RESID, 32529, 1024, 1024, "256x256 persistent"), (B.EPI_STORE, 13186, 3584, 5120, "256x256 persistent"),
+    (B.EPI_STORE, 8807, 3584, 5120, "256x256 persistent"), (B.EPI_GELU, 12877, 5120, 5120, "256x256 persistent"),
+    (B.EPI_RESID, 70138, 2048, 2048, "256x256 persistent"), (B.EPI_RESID, 14374, 2048, 2048, "256x256 persistent"),
+    (B.EPI_RESID, 21910, 1280, 1280, "256x320 persistent + 128x128")])
+def test_products_that_lose_when_cut_stay_whole(epi, m, n, k, kernel):
+    assert B.tcmv_op_gemm_kernel(epi, m, n, k) == kernel
+
+
 # side of one still image in patches -> kernels of the two products that accumulate (1280 wide, mlp 5120): slices of k where
 # they pay together with the norm that adds them, in the tiles that are faster (896 rows: 31 us a layer with 128x128 tiles, 37
 # with 64x64; 1760 rows: 51 unsplit, 51 in slices)
