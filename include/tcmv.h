@@ -230,11 +230,13 @@ int64_t tcmv_plan_row_map(const tcmv_plan *plan, int which, const int32_t **out)
 
 /* Which kernels the sizes of a plan lead to, for tests and for reading profiles (host only, nothing is launched).
  * tcmv_plan_key_norms: whether attention of this layer uses key norms: 0 no, 1 from a pass of their own, 2 from the
- * QKV product (or a negative error).  tcmv_plan_gemm_kernel: name of the bf16 kernel of a layer's product (kernel_class
+ * QKV product (or a negative error).  tcmv_plan_touches_weights: 1 where the attention launch of this layer also reads
+ * the weights of the products behind it into the caches, 0 where it does not.  tcmv_plan_gemm_kernel: name of the bf16 kernel of a layer's product (kernel_class
  * TCMV_K_QKV_GEMM, _OUT_GEMM, _FC1_GEMM or _FC2_GEMM): tile rows x columns, then "persistent" (one workgroup per CU),
  * "k/2" (two waves share the k-steps of a sub-tile) or "slices" (four slices of k); two names joined by " + " where whole
  * rounds of a persistent kernel take the first rows and another kernel the rest; NULL for fp32 models and errors. */
 int tcmv_plan_key_norms(const tcmv_plan *plan, int layer);
+int tcmv_plan_touches_weights(const tcmv_plan *plan, int layer);
 const char *tcmv_plan_gemm_kernel(const tcmv_plan *plan, int kernel_class, int layer);
 
 /* Stage 1 (Sec. 2.1: visual inputs are first preprocessed into pixels or frames;

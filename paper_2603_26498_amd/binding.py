@@ -73,6 +73,7 @@ SIGNATURES = {
     "tcmv_plan_meta": (C.c_void_p, [C.c_void_p, C.POINTER(C.c_size_t)]),
     "tcmv_plan_upload": (C.c_int, [C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]),
     "tcmv_plan_key_norms": (C.c_int, [C.c_void_p, C.c_int]),
+    "tcmv_plan_touches_weights": (C.c_int, [C.c_void_p, C.c_int]),
     "tcmv_plan_gemm_kernel": (C.c_char_p, [C.c_void_p, C.c_int, C.c_int]),
     "tcmv_preprocess": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
     "tcmv_encode": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t,
@@ -301,6 +302,10 @@ def tcmv_plan_gemm_kernel(plan, kernel_class, layer=0):
 
 def tcmv_plan_key_norms(plan, layer=0):
     return lib().tcmv_plan_key_norms(plan, layer)
+
+
+def tcmv_plan_touches_weights(plan, layer=0):
+    return lib().tcmv_plan_touches_weights(plan, layer)
 
 
 def tcmv_op_attention_workspace(dtype, cu_seqlens, d, heads):

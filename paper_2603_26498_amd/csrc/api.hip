@@ -285,6 +285,25 @@ LayerAttn layer_attn(const tcmv_plan* p, int l) {
   return a;
 }
 
+// Whether the attention launches of a pass bring the weights of the four products behind them nearer.  The weights of a small
+// request come from memory where a model and its request exceed the last-level cache, while its attention leaves CUs and the
+// memory idle.  Passes over one request, without and with: 256 tokens 2204 -> 1913 us, 1024 3868 -> 3631, 2304 6547 -> 6142;
+// 5 x 729 5303 -> 5254; windowed, 1024 tokens 3516 -> 3216, 2520 5519 -> 5416; from 4096 on nothing is gained.  Products of 256
+// rows: fc1 15.9 -> 12.2 us, QKV 11.6 -> 9.7, slices 10.9 -> 8.6; attention 8.7 -> 11.5.  The same from the norms in front of each
+// product cost them 2 - 3 us each (256 tokens: 2005 us a pass), from the products before 1 (1981).
+// A model that stays in the cache (of its 256 MB about 220 hold weights and activations from pass to pass) gains only where a
+// layer's weights fit the L2 caches of the XCDs, 32 MB with everything else there.  Passes without and with: encoders of 1280
+// (mlp 5120, 39 MB a layer), 4 layers, 576 tokens 322 / 326 us, 2304 719 / 729; 5 layers, 2304 tokens 997 / 934; 6 layers, 256
+// tokens 370 / 337; 2 layers of 2048 (101 MB), 64 tokens 113 / 126; 4 of 1152 (31 MB), 576 tokens 304 / 309; 8 of 1024 (25 MB),
+// 256 tokens 348 / 341; 12 of 768 (14 MB), 256 tokens 492 / 485.
+bool touches_weights(const tcmv_plan* p) {
+  const tcmv_model_desc& d = p->ctx->desc;
+  const EncodeWs ws = encode_ws(p);
+  const double layer = 2.0 * (4.0 * attn_width_of(d) + (d.mlp_gated ? 3.0 : 2.0) * d.mlp) * d.d;
+  const double pass = layer * d.layers + (double)(ws.total - ws.splitk_bytes) + 4.0 * (double)p->n_tokens * d.d;
+  return d.dtype == TCMV_BF16 && p->n_tokens < 4096 && (pass > 220e6 || layer < 28e6);
+}
+
 // Sizes and epilogue of a product of layer `l` (TCMV_K_QKV_GEMM .. TCMV_K_FC2_GEMM): everything the launcher chooses its
 // kernel by but the presence of `partial`.  The stage call adds the pointers.
 GemmArgs layer_product(const tcmv_plan* p, int kernel_class, int l) {
@@ -724,6 +743,11 @@ int tcmv_plan_key_norms(const tcmv_plan* p, int layer) {
   return a.fused ? 2 : a.key_norms ? 1 : 0;
 }
 
+int tcmv_plan_touches_weights(const tcmv_plan* p, int layer) {
+  if (!p || layer < 0 || layer >= p->ctx->desc.layers) return TCMV_E_INVALID_ARG;
+  return touches_weights(p) && !layer_attn(p, layer).key_norms;
+}
+
 const char* tcmv_plan_gemm_kernel(const tcmv_plan* p, int kernel_class, int layer) {
   if (!p || p->ctx->desc.dtype != TCMV_BF16 || layer < 0 || layer >= p->ctx->desc.layers) return nullptr;
   GemmArgs g = layer_product(p, kernel_class, layer);
@@ -824,13 +848,7 @@ int tcmv_encode(tcmv_ctx* ctx, const tcmv_plan* p, const void* d_meta, const voi
   // Slices of the last product that wait in the workspace: the next norm adds them to x first.
   const float* slices = nullptr;
   const float* slices_bias = nullptr;
-  // The weights of a small request come from memory (a model's exceed the last-level cache) while its attention leaves CUs
-  // and the memory idle: that launch brings those of the four products behind it nearer.  Passes over one request, without
-  // and with: 256 tokens 2204 -> 1913 us, 1024 3868 -> 3631, 2304 6547 -> 6142; 5 x 729 5303 -> 5254; windowed, 1024 tokens
-  // 3516 -> 3216, 2520 5519 -> 5416; from 4096 on nothing is gained.  Products of 256 rows: fc1 15.9 -> 12.2 us, QKV 11.6 -> 9.7,
-  // slices 10.9 -> 8.6; attention 8.7 -> 11.5.  The same from the norms in front of each product cost them 2 - 3 us each (256
-  // tokens: 2005 us a pass), from the products before 1 (1981).
-  const bool touching = bf && T < 4096;
+  const bool touching = touches_weights(p);
   auto bytes_of = [](int64_t rows, int64_t k) { return (uint32_t)std::min<int64_t>(rows * k * 2, 0xFFFFFF80ll); };
   auto norm = [&](const float* gm, const float* bt, void* y, int out_bf16) {
     const float* part = slices;

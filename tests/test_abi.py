@@ -305,6 +305,20 @@ def test_where_key_norms_pay(heads, dh, side, n, pays):
     assert norms < 2 or dh in (64, 80)          # only whole heads of these sizes fit the write-out of the QKV product
 
 
+# whether attention reads the weights behind it into the caches (one image, sides in patches): where model and request
+# exceed the last-level cache or a layer fits the L2 caches; the others lost up to 12 % (2 layers of 2048, 64 tokens: 113 us
+# without, 126 with)
+@pytest.mark.parametrize("layers,d,heads,mlp,side,touches", [
+    (12, 768, 12, 3072, (24, 24), 1), (8, 1024, 16, 4096, (16, 16), 1), (4, 1280, 16, 4352, (24, 24), 0), (4, 1280, 16, 5120, (48, 48), 0),
+    (2, 2048, 32, 8192, (8, 8), 0), (5, 1280, 16, 5120, (16, 16), 0), (5, 1280, 16, 5120, (32, 32), 1), (6, 1280, 16, 5120, (8, 8), 1),
+    (32, 1280, 16, 5120, (16, 16), 1), (32, 1280, 16, 5120, (63, 65), 0), (32, 1280, 16, 5120, (64, 64), 0)])
+def test_where_attention_reads_the_weights_behind_it(layers, d, heads, mlp, side, touches):
+    enc, pl = _host_plan(workloads.ModelDesc(layers=layers, d=d, heads=heads, mlp=mlp, patch=14, tpatch=1, merge=1), [side])
+    norms = B.tcmv_plan_key_norms(pl.handle, 0) > 0                    # with key norms a second launch would have to do it
+    assert B.tcmv_plan_touches_weights(pl.handle, 0) == (0 if norms else touches)
+    assert B.tcmv_plan_touches_weights(pl.handle, layers) < 0
+
+
 @pytest.mark.parametrize("heads,dh,side,norms", [(60, 64, 39, 0), (64, 64, 36, 0), (84, 64, 33, 0), (56, 64, 39, None), (60, 96, 66, 0), (28, 80, 99, None)])
 def test_attention_too_wide_for_the_pass_over_the_keys_goes_without_norms(heads, dh, side, norms):
     """The separate pass holds at most 512 chunk sums and norms of a row: wider models keep running, without the norms
