@@ -1114,9 +1114,8 @@ int op_attention_run(int dtype, const void* d_qkv, int d, int heads, const OpAtt
     a.q = q; a.k = q + d; a.ldqk = 3 * d; a.v = scratch + L.vt; a.ldv = L.t_vpad;
     a.scale = (float)(1.4426950408889634 / std::sqrt((double)dh));
     a.prescaled = 0;                               // the caller's queries are unscaled
-    if (L.bq == 64) {                              // these items do without key norms
-      if (!knorm_available(heads, dh)) return TCMV_E_HIP;
-    } else {
+    // 64-row items do without key norms, and so does attention wider than the pass over the keys holds
+    if (L.bq != 64 && knorm_available(heads, dh)) {
       uint32_t* kmax = reinterpret_cast<uint32_t*>(scratch + L.kmax);
       e = launch_fill_zero(kmax, L.kmax_bytes, s);
       if (e != hipSuccess) return TCMV_E_HIP;

@@ -945,7 +945,7 @@ float norm_cost(const GemmArgs& a, const TileKernel& t, int64_t m) {
 // Estimate for a persistent kernel over whole rounds of tiles, where tile_cost falls short (the chip clocks lower when every
 // CU computes): microseconds a round, by k-tiles and by what the write-out does, and for the last, partly filled round.
 // Products that accumulate are narrow (a model's width) and read more of A from memory for a tile: they have constants of
-// their own, fitted to 2400 products of 3000 - 102000 rows (off by 6 and 9 % r.m.s.); those of the others are least squares
+// their own, fitted to 2400 products of 3000 - 102000 rows (off by 6 and 8 % r.m.s.); those of the others are least squares
 // over 396 products each of 2500 - 102000 rows, n 1024 - 8192, k 1024 - 5120, weights from memory (3.8 and 3.6 %).
 struct RoundCost { float base, full_k, part_k, part_k_fill, resid, store, gelu, qkv, gated; };
 constexpr RoundCost kRoundCosts[2][2] = {                          // 256x320, 256x256; accumulating, the others
@@ -1099,7 +1099,9 @@ static hipError_t launch_part(GemmKernel gk, const GemmArgs& args, hipStream_t s
     a.rope_inv = 0xFFFFFFFFu / (uint32_t)a.rope_dh + 1;
   }
   if (is_persistent(gk) && a.epi == EPI_RESID && (double)a.m * (double)a.n * 4.0 > 400e6) {
-    GemmArgs g = a;                                 // an output larger than the last-level cache: see wave_epilogue
+    // An output larger than the last-level cache: see wave_epilogue.  By the rows of this part: heads of 377 MB before a rest
+    // that takes the output above 400 lose by it (87000 - 91000 x 1152 x 1280 363 -> 376 us, k 4352 866 -> 879).
+    GemmArgs g = a;
     g.epi = EPI_RESID_AHEAD;
     return gk == GK_P320 ? launch_persist<256, 320, 4, 2>(g, s) : launch_persist<256, 256, 2, 4>(g, s);
   }
