@@ -232,7 +232,7 @@ int64_t tcmv_plan_row_map(const tcmv_plan *plan, int which, const int32_t **out)
  * tcmv_plan_key_norms: whether attention of this layer uses key norms: 0 no, 1 from a pass of their own, 2 from the
  * QKV product (or a negative error).  tcmv_plan_touches_weights: 1 where the attention launch of this layer also reads
  * the weights of the products behind it into the caches, 0 where it does not.  tcmv_plan_gemm_kernel: name of the bf16 kernel of a layer's product (kernel_class
- * TCMV_K_QKV_GEMM, _OUT_GEMM, _FC1_GEMM or _FC2_GEMM): tile rows x columns, then "persistent" (one workgroup per CU),
+ * TCMV_K_QKV_GEMM, _OUT_GEMM, _FC1_GEMM or _FC2_GEMM; TCMV_K_EMBED_GEMM for any layer): tile rows x columns, then "persistent" (one workgroup per CU),
  * "k/2" (two waves share the k-steps of a sub-tile) or "slices" (four slices of k); two names joined by " + " where whole
  * rounds of a persistent kernel take the first rows and another kernel the rest; NULL for fp32 models and errors. */
 int tcmv_plan_key_norms(const tcmv_plan *plan, int layer);

@@ -304,7 +304,7 @@ bool touches_weights(const tcmv_plan* p) {
   return d.dtype == TCMV_BF16 && p->n_tokens < 4096 && (pass > 220e6 || layer < 28e6);
 }
 
-// Sizes and epilogue of a product of layer `l` (TCMV_K_QKV_GEMM .. TCMV_K_FC2_GEMM): everything the launcher chooses its
+// Sizes and epilogue of a product of layer `l` (TCMV_K_QKV_GEMM .. TCMV_K_FC2_GEMM) or of the patch embedding: everything the launcher chooses its
 // kernel by but the presence of `partial`.  The stage call adds the pointers.
 GemmArgs layer_product(const tcmv_plan* p, int kernel_class, int l) {
   const tcmv_model_desc& d = p->ctx->desc;
@@ -313,6 +313,9 @@ GemmArgs layer_product(const tcmv_plan* p, int kernel_class, int l) {
   GemmArgs g{};
   g.m = p->n_tokens;
   switch (kernel_class) {
+    case TCMV_K_EMBED_GEMM:
+      g.m = p->n_patch_rows; g.lda = g.k = (int)p->ctx->k_pad; g.ldc = g.n = d.d; g.epi = EPI_EMBED;
+      break;
     case TCMV_K_QKV_GEMM:
       g.lda = g.k = d.d; g.n = 3 * da; g.epi = EPI_QKV;
       g.ldc = bf ? 2 * da : 3 * d.d;
@@ -749,7 +752,8 @@ int tcmv_plan_touches_weights(const tcmv_plan* p, int layer) {
 }
 
 const char* tcmv_plan_gemm_kernel(const tcmv_plan* p, int kernel_class, int layer) {
-  if (!p || p->ctx->desc.dtype != TCMV_BF16 || layer < 0 || layer >= p->ctx->desc.layers) return nullptr;
+  if (!p || p->ctx->desc.dtype != TCMV_BF16) return nullptr;
+  if (kernel_class != TCMV_K_EMBED_GEMM && (layer < 0 || layer >= p->ctx->desc.layers)) return nullptr;
   GemmArgs g = layer_product(p, kernel_class, layer);
   if (g.m <= 0) return nullptr;
   // only looked at for being there
@@ -831,9 +835,8 @@ int tcmv_encode(tcmv_ctx* ctx, const tcmv_plan* p, const void* d_meta, const voi
   int kblock = 0;                                  // key-norm block of the next layer that uses one
   // patch embedding (+ position), CLS rows
   {
-    GemmArgs g{};
-    g.a = d_patches; g.lda = ctx->k_pad; g.w = ctx->w.w_pe; g.bias = reinterpret_cast<const float*>(ctx->w.b_pe);
-    g.c = x; g.ldc = d.d; g.m = p->n_patch_rows; g.n = d.d; g.k = (int)ctx->k_pad; g.epi = EPI_EMBED;
+    GemmArgs g = layer_product(p, TCMV_K_EMBED_GEMM, 0);
+    g.a = d_patches; g.w = ctx->w.w_pe; g.bias = reinterpret_cast<const float*>(ctx->w.b_pe); g.c = x;
     g.dst_row = dev<int32_t>(d_meta, p->off_prow_dst); g.pos_idx = dev<int32_t>(d_meta, p->off_prow_pos);
     g.pos0 = reinterpret_cast<const float*>(ctx->w.pos0); g.pos1 = reinterpret_cast<const float*>(ctx->w.pos1);
     g.pos_kind = d.pos;

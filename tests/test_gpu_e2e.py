@@ -11,6 +11,7 @@ import torch
 
 import oracle
 import workloads
+from oracle import encoder as oe
 from paper_2603_26498_amd import binding as B
 from paper_2603_26498_amd.runtime import VisionEncoder
 from util import assert_tokens_close
@@ -232,13 +233,14 @@ def test_long_segments_take_the_norm_bounded_attention_path(std):
     (2, 64, (57, 57), 1, "128x128"), (6, 64, (37, 87), 1, "128x128 k/2"), (18, 64, (36, 33), 2, "192x256"), (4, 64, (35, 38), 6, "256x128"),
     (8, 64, (39, 36), 4, "256x256 persistent"), (4, 80, (96, 43), 2, "256x160"), (8, 80, (40, 33), 6, "256x320 persistent")])
 @pytest.mark.parametrize("spread", [0.36, 1.43])
-def test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(heads, dh, side, n, kernel, spread):
-    """Two layers with rotary positions, RMSNorm and gated MLP, ragged rows: the QKV product squares and sums the keys on
+@pytest.mark.parametrize("pos", ["rope2d", "none"])
+def test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(heads, dh, side, n, kernel, spread, pos):
+    """Two layers with rotary positions or without (kernels of their own), RMSNorm and gated MLP, ragged rows: the QKV product squares and sums the keys on
     their way out, into alternating tables that the attention of the layer before clears.  Weights of standard deviation
     spread / sqrt(d) give queries and keys of standard deviation `spread` at every width, scores of spread^2 (bounded by
     the norms, or not).  Queries and keys are rounded to bf16 (2^-9 of each), which moves a score by about 2^-8 of itself and
     its probability by as much: 1 % for scores near 2, inside the bar; scores of 7 (spread 2.7) would miss it."""
-    desc = workloads.ModelDesc(layers=2, d=heads * dh, heads=heads, mlp=128, patch=14, tpatch=1, merge=1, pos="rope2d", norm="rms", gated=1)
+    desc = workloads.ModelDesc(layers=2, d=heads * dh, heads=heads, mlp=128, patch=14, tpatch=1, merge=1, pos=pos, norm="rms", gated=1)
     rng = np.random.default_rng(heads + dh)
     items = [workloads.Item(workloads.IMAGE, 1, 14 * side[0], 14 * side[1], 14 * side[0], 14 * side[1],
                             workloads.random_frames(rng, 1, 14 * side[0], 14 * side[1])) for _ in range(n)]
@@ -310,9 +312,136 @@ def test_softmax_reference_moves_between_keys(grid, n, heads, rows, border):
     assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, "two kinds of tokens")
 
 
-def test_qkv_product_in_whole_rounds_and_the_rest():
+def _first_attention(wl):
+    """Queries, keys and values of the first layer and the weights of its softmax in log2 units, by the reference."""
+    res = oracle.run(wl, stages=("preprocess",))
+    d, dh, g = wl.desc.d, wl.desc.d // wl.desc.heads, lambda n: wl.weights["l0." + n].astype(np.float64)
+    x = oe.norm(wl.desc, oe.embed(res["patches"], res["grids"], wl.desc, wl.weights), g("ln1_g"), g("ln1_b"))
+    qkv = x @ g("w_qkv").T + g("b_qkv")
+    q, k, v = (qkv[:, i * d:(i + 1) * d].reshape(-1, wl.desc.heads, dh).transpose(1, 0, 2) for i in range(3))
+    return q @ k.transpose(0, 2, 1) * (np.log2(np.e) / dh ** 0.5), v
+
+
+@pytest.mark.parametrize("heads,dh", [(4, 64), (4, 80), (2, 96)])
+@pytest.mark.parametrize("row", [2, 6, 10, 14])
+def test_softmax_reference_moves_inside_a_group_of_keys(row, heads, dh):
+    """256 keys, a tile of 64 for each of four groups of waves, black above the given picture row and white below it: the border
+    lies between the two blocks of 32 keys of one group, whose reference has to move there, with what it has summed by then;
+    the groups behind it start from the reference of the black keys and move before they begin.  Where the white keys score
+    higher, by more than the 8 that leave a reference alone, sums that do not move along would give the black keys of that
+    group as much weight as the white ones: an error that this bar sees."""
+    desc = workloads.ModelDesc(layers=1, d=heads * dh, heads=heads, mlp=128, patch=14, tpatch=1, merge=1)
+    f = np.zeros((1, 224, 224, 3), np.uint8)
+    f[:, 14 * row:] = 255
+    wl = workloads.Workload("two_kinds", desc, [workloads.Item(workloads.IMAGE, 1, 224, 224, 224, 224, f)],
+                            workloads.make_weights(desc, 36, std=2.5 / desc.d ** 0.5, random_affine=True))
+    s, v = _first_attention(wl)
+    b = 16 * row                                             # the first white key; black ones from b - 32 on share its tile
+    rise = s[:, :, b:b + 32].max(2) - s[:, :, b - 32:b].max(2)
+    moved = rise > 9
+    assert b % 64 == 32 and moved.any() and (rise < -9).any()
+    p = np.exp2(s - s.max(2, keepdims=True))
+    right = (p / p.sum(2, keepdims=True)) @ v
+    p[:, :, b - 32:b] = np.where(moved[:, :, None], 1.0, p[:, :, b - 32:b])
+    wrong = (p / p.sum(2, keepdims=True)) @ v
+    assert np.abs(wrong - right).max() > 0.1 * np.abs(right).max()
+    ref = oracle.run(wl, workers=4)
+    enc, pl, patches, hidden, out = run_gpu(wl)
+    assert B.tcmv_op_attention_rows(B.TCMV_BF16, pl.cu_seqlens, heads * dh, heads) == 64
+    assert_tokens_close(hidden.cpu().numpy(), ref["hidden"], 2e-2, 0.999, "two kinds of tokens in a tile")
+
+
+# colours of a picture's patches: what the scores of its keys become in the first head
+_PLAIN, _LIGHT, _MINUS_INF, _PLUS_INF = (0, 0, 0), (255, 255, 255), (0, 255, 0), (255, 0, 0)
+
+
+def _infinite_scores_model(heads, dh):
+    """One layer in which the key of a red patch has +inf in its first element, of a green one -inf, of a black or white one 0,
+    and every query has a positive number there (first head; the others are ordinary).  Elements 0 and 1 of the
+    embedding are the means of the red and green channels, the key element is 2^126 times their difference behind the norm."""
+    desc = workloads.ModelDesc(layers=1, d=heads * dh, heads=heads, mlp=128, patch=14, tpatch=1, merge=1)
+    w = workloads.make_weights(desc, 39, std=1.0 / desc.d ** 0.5, random_affine=True)
+    w["w_pe"] = np.random.default_rng(7).normal(0, 0.01, w["w_pe"].shape).astype(np.float32)
+    w["w_pe"] = workloads.snap_to_bf16_grid(w["w_pe"])
+    channel = oracle.run(workloads.Workload("channels", desc, [workloads.Item(workloads.IMAGE, 1, 14, 14, 14, 14, np.array([[[255, 0, 0]]], np.uint8)
+                         .repeat(14, 0).repeat(14, 1)[None])], w), stages=("preprocess",))["patches"][0][0]
+    red = channel > 0
+    green = oracle.run(workloads.Workload("channels", desc, [workloads.Item(workloads.IMAGE, 1, 14, 14, 14, 14, np.array([[[0, 255, 0]]], np.uint8)
+                       .repeat(14, 0).repeat(14, 1)[None])], w), stages=("preprocess",))["patches"][0][0] > 0
+    assert red.sum() == green.sum() == 196
+    w["w_pe"][:2] = 0
+    w["w_pe"][0, red] = w["w_pe"][1, green] = 2.0 ** -6
+    w["b_pe"] = np.random.default_rng(8).normal(0, 1, desc.d).astype(np.float32)
+    w["b_pe"][:2] = 0
+    w["l0.ln1_g"][:2], w["l0.ln1_b"][:2] = 1, 0
+    w["l0.w_qkv"][0] = 0                                     # first element of the first query: a bias
+    w["l0.b_qkv"][0] = 1
+    w["l0.w_qkv"][desc.d] = 0                                # of the first key
+    w["l0.w_qkv"][desc.d, 0], w["l0.w_qkv"][desc.d, 1] = 2.0 ** 126, -2.0 ** 126
+    w["l0.b_qkv"][desc.d] = 0
+    return desc, w
+
+
+def _picture(h, w, rng, *runs):
+    """Patches black or white at random, then (first key, last key, colour) runs."""
+    c = np.where(rng.integers(0, 2, (h * w, 1)) > 0, np.array(_LIGHT), np.array(_PLAIN)).astype(np.uint8)
+    for a, b, colour in runs:
+        c[a:b] = colour
+    return workloads.Item(workloads.IMAGE, 1, 14 * h, 14 * w, 14 * h, 14 * w, c.reshape(h, w, 3).repeat(14, 0).repeat(14, 1)[None])
+
+
+@pytest.mark.parametrize("heads,dh", [(2, 64), (4, 80)])
+@pytest.mark.parametrize("rows,h,w,more", [(64, 16, 16, 0), (128, 20, 35, 0), (128, 24, 24, 12)])
+def test_attention_with_infinite_scores(rows, h, w, more, heads, dh):
+    """Keys that score -inf weigh nothing wherever they lie (the first keys, a whole tile, a whole group of waves' keys, all but
+    one); where all keys score -inf, or one +inf, softmax has no value and the segment's rows are NaN.  The other
+    segments of the launch are what they are without them."""
+    desc, wts = _infinite_scores_model(heads, dh)
+    rng = np.random.default_rng(rows + h)
+    n, half = h * w, (h * w + 127) // 128 * 64                # keys of the first of two groups, in whole tiles
+    items = [_picture(h, w, rng, (0, 40, _MINUS_INF)), _picture(h, w, rng, (0, 64, _MINUS_INF)), _picture(h, w, rng, (64, 128, _MINUS_INF)),
+             _picture(h, w, rng, (0, half, _MINUS_INF)), _picture(h, w, rng, (half, n, _MINUS_INF)), _picture(h, w, rng, (0, 77, _MINUS_INF), (78, n, _MINUS_INF)),
+             _picture(h, w, rng), _picture(h, w, rng, (0, n, _MINUS_INF)), _picture(h, w, rng, (5, 6, _PLUS_INF)), _picture(h, w, rng, (n - 1, n, _PLUS_INF))]
+    items += [_picture(h, w, rng, (32 * i, 32 * i + 48, _MINUS_INF)) for i in range(more)]
+    wl = workloads.Workload("infinities", desc, items, wts)
+    ref = oracle.run(wl, workers=4)["hidden"]                 # 64-bit numbers hold what is infinite on the GPU
+    pre = oracle.run(wl, stages=("preprocess",))
+    x = oe.embed(pre["patches"], pre["grids"], desc, wts)
+    ln = oe.layernorm(x, wts["l0.ln1_g"].astype(np.float64), wts["l0.ln1_b"].astype(np.float64), desc.ln_eps)[:, :2]
+    # each of the two products is finite in 32 bits, their difference of a coloured patch is not
+    assert np.all(np.abs(ln) < 3.9) and np.all((ln[:, 0] == ln[:, 1]) | (np.abs(ln[:, 0] - ln[:, 1]) > 4.1))
+    enc, pl, patches, hidden, out = run_gpu(wl)
+    assert B.tcmv_op_attention_rows(B.TCMV_BF16, pl.cu_seqlens, heads * dh, heads) == rows and B.tcmv_plan_key_norms(pl.handle, 0) == 0
+    got = hidden.cpu().numpy()
+    for i, (a, b) in enumerate(zip(pl.cu_seqlens, pl.cu_seqlens[1:])):
+        if 7 <= i <= 9:
+            assert np.isnan(got[a:b]).all(), i
+        else:
+            assert_tokens_close(got[a:b], ref[a:b], 2e-2, 0.999, f"segment {i}")
+
+
+@pytest.mark.parametrize("pos", ["rope2d", "none"])
+def test_qkv_product_in_whole_rounds_and_the_rest(pos):
     """Rotary factors, transposed values and key norms of the rows behind the whole rounds, which a second kernel computes."""
-    test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(16, 80, (33, 33), 6, "256x320 persistent + 128x160", 0.36)
+    test_key_norms_from_the_write_out_of_every_kernel_that_computes_them(16, 80, (33, 33), 6, "256x320 persistent + 128x160", 0.36, pos)
+
+
+@pytest.mark.parametrize("pos", ["sep2d", "learned1d"])
+def test_patch_embedding_in_whole_rounds_and_the_rest(pos):
+    """The serving batch's 16656 patches at full width: 13056 in whole rounds of tiles, the rest on another kernel that scatters
+    its rows and reads its positions from where the first stopped.  No layers behind it: every row is the fp32 sum itself."""
+    desc = workloads.ModelDesc(layers=0, d=1280, heads=16, mlp=128, patch=14, tpatch=2, merge=2 if pos == "sep2d" else 1, pos=pos, max_pos=4300)
+    rng = np.random.default_rng(47)
+    sizes = [(1, 56, 64), (2, 48, 44), (1, 60, 60), (1, 40, 66), (6, 28, 12), (1, 20, 28), (1, 4, 8)]    # frames / 2 for videos, patches
+    items = []
+    for t, h, w in sizes:
+        n = 2 * t if t > 1 else 1
+        items.append(workloads.Item(workloads.VIDEO if t > 1 else workloads.IMAGE, n, 14 * h, 14 * w, 14 * h, 14 * w, workloads.random_frames(rng, n, 14 * h, 14 * w)))
+    wl = workloads.Workload("embedding", desc, items, workloads.make_weights(desc, 40, random_affine=True))
+    ref = oracle.run(wl, workers=4)
+    enc, pl, patches, hidden, out = run_gpu(wl)
+    assert B.tcmv_plan_gemm_kernel(pl.handle, "embed_gemm") == "256x256 persistent + 128x160"
+    assert np.abs(hidden.cpu().numpy() - ref["hidden"]).max() <= 1e-4 * max(1.0, np.abs(ref["hidden"]).max())
 
 
 def test_rows_behind_whole_rounds_in_slices_of_k():

@@ -497,6 +497,20 @@ def test_gelu_epilogue_far_from_zero():
     assert np.abs(got[:, x < 0]).max() <= 1e-17          # 9 * Phi(-9) = 1e-18
 
 
+def test_gelu_epilogue_keeps_overflow_visible():
+    """Infinite sums and NaN leave GELU as NaN on the bf16 path (inf * 0; the erf form of the fp32 path agrees but for +inf,
+    which it keeps): an overflow does not turn into an ordinary number.  Their neighbours are untouched."""
+    m, n, k = 64, 512, 64
+    x = np.tile(np.array([np.inf, 1.0, -np.inf, -1.0, np.nan, 3.0, 0.0, -3.0], np.float32), n // 8)
+    c = torch.full((m, n), 7.0, dtype=torch.bfloat16, device=DEV)
+    B.tcmv_op_gemm(B.TCMV_BF16, B.EPI_GELU, torch.zeros((m, k), dtype=torch.bfloat16, device=DEV), torch.zeros((n, k), dtype=torch.bfloat16, device=DEV),
+                   dev(x), c, m, n, k)
+    sync()
+    got, ok = c.float().cpu().numpy(), np.isfinite(x)
+    assert np.isnan(got[:, ~ok]).all()
+    assert np.abs(got[:, ok] - oe.gelu(x[ok].astype(np.float64))).max() <= 2.0 ** -8 * 3
+
+
 def test_attention_mixed_norm_bounds_in_one_launch():
     """Some (segment, head, query tile) combinations have provably small scores and are exponentiated without
     a softmax reference, others in the same launch are not: head 0 has large queries, one block of query rows
@@ -588,6 +602,36 @@ def test_attention_f32_infinities_stay_where_they_belong(dh):
     assert np.array_equal(np.isinf(got), np.isinf(ref)) and np.isinf(ref).sum() == 17
     ok = np.isfinite(ref)
     assert np.abs(got[ok] - ref[ok]).max() <= 2e-5 * max(1.0, np.abs(ref[ok]).max())
+
+
+@pytest.mark.parametrize("dh", [32, 64, 80, 96])
+@pytest.mark.parametrize("lens,rows", [([256, 130, 64, 100, 33, 200, 77], 64), ([600, 300, 129, 100, 33, 200, 77], 128)])
+def test_attention_bf16_infinities_stay_where_they_belong(lens, rows, dh):
+    """Keys that score -inf weigh nothing: a run of them, whole tiles, those of whole groups of waves (64-row items: also the
+    first keys of a segment); a segment whose keys all score -inf, or one of whose keys scores +inf or is not a number, has
+    no softmax in that head.  Nothing reaches another head or segment."""
+    rng = np.random.default_rng(dh + rows)
+    heads = 2
+    d = heads * dh
+    cu = [0] + [int(c) for c in np.cumsum(lens)]
+    assert B.tcmv_op_attention_rows(B.TCMV_BF16, cu, d, heads) == rows
+    qkv = _qkv(rng, cu[-1], d, 1.0, "bf16")
+    qkv[:, 0] = 1.0 + np.abs(qkv[:, 0])                    # first element of the first head's queries: positive
+    qkv = bf16_grid(qkv)
+    first = 0 if rows == 64 else 40                        # an undivided loop sets its reference from the first 32 keys
+    qkv[first:128, d] = -np.inf                            # runs of keys of the first head
+    qkv[cu[1] + 64:cu[2], d] = -np.inf
+    qkv[cu[2] + 32:cu[2] + 64, d] = -np.inf
+    qkv[cu[3]:cu[4], d] = -np.inf                          # every key
+    qkv[cu[4] + 7, d] = np.inf
+    qkv[cu[5] + 150, d] = np.nan
+    x = qkv.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        ref = oe.attention(x[:, :d], x[:, d:2 * d], x[:, 2 * d:], cu, heads)
+    got = _attn("bf16", qkv, cu, d, heads)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(ref).sum() == (cu[6] - cu[3]) * dh
+    ok = np.isfinite(ref)
+    assert np.isfinite(got[ok]).all() and np.abs(got[ok] - ref[ok]).max() <= 1.2e-2 * np.abs(ref[ok]).max()
 
 
 # one product for every tile kernel and epilogue, ragged in both directions, with short contractions (fewer k-tiles than
