@@ -46,6 +46,7 @@ struct tcmv_plan {
   std::vector<int32_t> row_seg, row_seg_win;   // hidden row -> index of its segment / window (key-norm table row)
   int n_windows = 0;
   int64_t max_win_len = 0;          // longest window (tokens)
+  int64_t max_seg_len = 0;          // longest segment
   std::vector<float> lut;             // [3][256]
   std::vector<PreStrip> strips;       // preprocessing work of the strip kernel: copied strips, then (appended at the end of planning) the resampled ones
   std::vector<PreStrip> strips_resampled;
@@ -83,10 +84,13 @@ int fail_hip(tcmv_ctx* ctx, hipError_t e, const char* what) {
 // tiles per wave (256 rows with 4 waves, 512 with 8); 512-row items stage every K/V tile once per
 // CU instead of twice and are used when rounding the segments up to 512 rows wastes little.
 int attn_bq_bf16(int dh, int heads, const std::vector<int64_t>& seg_len) {
-  // one tiny request: 64-row items whose keys, at most four tiles, are shared by four groups of waves
+  // One tiny request: 64-row items whose keys, four tiles, are shared by four groups of waves.  With fewer tiles the groups only
+  // meet (12 layers of 640, heads of 80, passes with 128-row items and 64-row ones: 64 tokens 403 / 432 us, 192 456 / 468), and
+  // more items leave no CUs to touch the next weights from (32 layers of 1280: 256 tokens 1885 / 1818, 3 x 256 2750 / 2906,
+  // 4 x 256 3137 / 3502).
   int64_t items64 = 0, longest = 0;
   for (int64_t n : seg_len) { items64 += (n + 63) / 64; longest = std::max(longest, n); }
-  if (longest <= 256 && items64 * heads <= 256) return 64;
+  if (longest > 192 && longest <= 256 && items64 * heads <= 160) return 64;
   if (dh > 80) return 128;
   int64_t rows = 0, padded = 0, items256 = 0, items512 = 0;
   for (int64_t n : seg_len) { rows += n; padded += (n + 511) / 512 * 512; items256 += (n + 255) / 256; items512 += (n + 511) / 512; }
@@ -619,6 +623,7 @@ int tcmv_plan_create(tcmv_ctx* ctx, const tcmv_item* items, int n_items, tcmv_pl
   p->norm_bound_win = d.dtype == TCMV_BF16 && long_enough(win_len);
   p->n_windows = (int)win_start.size();
   for (int64_t n : win_len) p->max_win_len = std::max(p->max_win_len, n);
+  for (int64_t n : seg_len) p->max_seg_len = std::max(p->max_seg_len, n);
   // normalisation table: (v/255 - mean)/std in double, rounded to fp32, then to bf16 for bf16 models
   p->lut.resize(3 * 256);
   for (int c = 0; c < 3; ++c)
@@ -906,6 +911,7 @@ int tcmv_encode(tcmv_ctx* ctx, const tcmv_plan* p, const void* d_meta, const voi
       else { a.work = dev<AttnWork>(d_meta, p->off_work); a.n_work = (int)p->work.size(); }
       a.heads = d.heads; a.dh = dh; a.t_total = T; a.out = xn; a.ldo = da;
       a.bq = windowed ? kAttnBQ_window : p->bq;
+      a.longest = windowed ? p->max_win_len : p->max_seg_len;
       if (bf) {
         const uint16_t* qk = reinterpret_cast<const uint16_t*>(qkv);
         a.q = qk; a.k = qk + da; a.ldqk = 2 * da; a.v = vt; a.ldv = p->ldvt();
@@ -1044,7 +1050,7 @@ const char* tcmv_op_gemm_kernel(int epilogue, int64_t m, int n, int k) {
 namespace {
 // Index data (built on the host, uploaded by the caller): [row -> transposed-V column][work list][row -> segment].
 // Scratch: [transposed V][key-norm table + flag].
-struct OpAttnLayout { size_t vcol, work, rseg, index_total; size_t vt, kmax, kmax_bytes, ws_total; int64_t t_vpad; int64_t T; int bq; size_t n_seg; size_t n_work; };
+struct OpAttnLayout { size_t vcol, work, rseg, index_total; size_t vt, kmax, kmax_bytes, ws_total; int64_t t_vpad; int64_t T; int bq; int64_t longest; size_t n_seg; size_t n_work; };
 OpAttnLayout op_attn_layout(int dtype, const int64_t* cu, int n_seg, int d, int heads, std::vector<int32_t>* vcol,
                             std::vector<AttnWork>* work, std::vector<int32_t>* rseg = nullptr) {
   OpAttnLayout L{};
@@ -1054,6 +1060,7 @@ OpAttnLayout op_attn_layout(int dtype, const int64_t* cu, int n_seg, int d, int 
     const int64_t len = cu[s + 1] - cu[s];
     if (len <= 0) continue;
     ss.push_back(cu[s]); sl.push_back(len); sv.push_back(vp);
+    L.longest = std::max(L.longest, len);
     vp += (len + kVtAlign - 1) / kVtAlign * kVtAlign;
   }
   L.T = n_seg > 0 ? cu[n_seg] : 0;
@@ -1106,7 +1113,7 @@ int op_attention_run(int dtype, const void* d_qkv, int d, int heads, const OpAtt
   AttnArgs a{};
   a.work = reinterpret_cast<const AttnWork*>(idx + L.work); a.n_work = (int)L.n_work;
   a.heads = heads; a.dh = dh; a.t_total = L.T; a.out = d_out; a.ldo = d;
-  a.bq = L.bq;
+  a.bq = L.bq; a.longest = L.longest;
   hipError_t e;
   if (dtype == TCMV_BF16) {
     const uint16_t* q = reinterpret_cast<const uint16_t*>(d_qkv);

@@ -777,10 +777,12 @@ template <int DH, int NT, int NWV, bool PRESC, bool FAST, int KG, int NST>
 __global__ __launch_bounds__(NWV * KG * 64, 1) void attn_bf16_groups_kernel(AttnArgs a) { attention<DH, NT, NWV, PRESC, FAST, KG, NST>(a); }
 
 // Small requests without key norms, keys split over groups of waves.  One image of 1120 tokens, 16 heads of 80 (144 items
-// of 128 rows): 24.7 -> 21.4 us a layer; 256 tokens: 9.6 -> 8.7, of which 4.6 pass before the first scores and behind the last.
-// 64-row items of segments of at most 256 keys (a tile of keys for each of four groups, so no ring), otherwise 128-row
+// of 128 rows): 24.7 -> 21.4 us a layer, 22.0 where the launch also touches weights; 576 tokens 14.8 -> 14.0.
+// 64-row items of segments of 193 - 256 keys (a tile of keys for each of four groups, so no ring): 9.4 us with and without
+// groups, but one workgroup on a CU leaves the others to the touching ones (11.0 against 12.8 us with it).  Otherwise 128-row
 // items as long as every one has a CU of its own: from two on a CU on, the rings of a second group do not fit LDS and
-// the other workgroup covers the waits anyway.
+// the other workgroup covers the waits anyway.  Up to three tiles of keys the groups gain less than their meeting costs (16
+// heads of 80, 64 keys: 4.9 us without groups, 7.6 with; 16 x 64 keys, 24 layers of 1024: 1763 us a pass, 1940 with two groups).
 template <bool PRESC>
 static hipError_t launch_attn_groups(AttnArgs a, hipStream_t s) {
   const unsigned grid = a.item_blocks + touch_blocks(a.touch, 512, 256 - (int64_t)a.item_blocks);
@@ -835,7 +837,8 @@ hipError_t launch_attn_bf16(const AttnArgs& args, hipStream_t s) {
     const hipError_t e = a.prescaled ? launch_attn_t<true, true>(a, s) : launch_attn_t<false, true>(a, s);
     if (e != hipSuccess) return e;
   }
-  if (a.bq == 64 || (a.bq == 128 && !a.kmax2 && total <= 256))
+  if (a.bq == 64 && (a.longest <= 0 || a.longest > 4 * BKV)) return hipErrorInvalidValue;      // a tile of keys for each group
+  if (a.bq == 64 || (a.bq == 128 && !a.kmax2 && total <= 256 && a.longest > 3 * BKV))
     return a.prescaled ? launch_attn_groups<true>(a, s) : launch_attn_groups<false>(a, s);
   return a.prescaled ? launch_attn_t<true, false>(a, s) : launch_attn_t<false, false>(a, s);
 }

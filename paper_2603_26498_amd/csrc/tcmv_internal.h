@@ -117,6 +117,7 @@ struct AttnArgs {
   int heads, dh;
   int bq;                                        // query rows per work item the list was built with (bf16: 64, 128, 256 or 512)
   int64_t t_total;                               // rows of q/k (for clamping)
+  int64_t longest;                               // bf16: keys of the longest segment of the work list
   float scale;                                   // softmax scale * log2(e); 1 when the queries already carry it
   int prescaled;                                 // bf16 path: the queries already carry the scale
   const uint32_t* kmax2;                         // bf16 path, may be null: [segments][heads] largest squared key norm (float bits)

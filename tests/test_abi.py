@@ -232,6 +232,16 @@ def test_rows_of_an_attention_work_item(heads, dh, lens, rows):
     assert B.tcmv_op_attention_rows(B.TCMV_BF16, cu, heads * dh, heads) == rows
 
 
+# tiny requests: 64-row items over four groups of waves only with a tile of keys for each group and CUs to spare; elsewhere
+# they lost time (8 x 64 tokens 3 %, 4 x 256 tokens of 16 heads 1 % and 8 % of what touching weights gains)
+@pytest.mark.parametrize("heads,dh,lens,rows", [
+    (16, 80, [256], 64), (16, 80, [193], 64), (16, 80, [192], 128), (16, 80, [64], 128), (16, 80, [1], 128), (16, 80, [64] * 4, 128),
+    (16, 80, [256] * 2, 64), (16, 80, [256] * 3, 128), (16, 64, [256] * 4, 128), (16, 80, [257], 128), (6, 64, [256] * 6, 64)])
+def test_rows_of_tiny_requests(heads, dh, lens, rows):
+    cu = [0] + [int(c) for c in np.cumsum(lens)]
+    assert B.tcmv_op_attention_rows(B.TCMV_BF16, cu, heads * dh, heads) == rows
+
+
 def _host_plan(desc, sizes):
     """Plan of still images given in patches (no weights, nothing uploaded) and the encoder that owns it."""
     p = desc.patch

@@ -217,10 +217,10 @@ def test_attention_large_work_items(lens, qs, big_head, rows):
     assert np.sqrt(((got - ref) ** 2).mean()) <= 4e-3 * np.sqrt((ref ** 2).mean())
 
 
-@pytest.mark.parametrize("lens,heads,dh,rows", [([64, 37, 64], 64, 64, 64), ([100], 120, 32, 64), ([300], 60, 64, 128), ([700, 60], 60, 64, 128), ([1250], 60, 64, 256)])
+@pytest.mark.parametrize("lens,heads,dh,rows", [([64, 37, 64], 64, 64, 128), ([100], 120, 32, 128), ([300], 60, 64, 128), ([700, 60], 60, 64, 128), ([1250], 60, 64, 256)])
 def test_attention_wider_than_the_pass_over_the_keys(lens, heads, dh, rows):
     """More heads than the separate pass over the keys holds: the operator goes without key norms, as the encoder does, with
-    64-row items, 128-row items (alone on a CU over two groups of keys) and 256-row items."""
+    128-row items, over one and two groups of keys, and with 256-row items."""
     d, cu = heads * dh, [0] + [int(c) for c in np.cumsum(lens)]
     qkv = _qkv(np.random.default_rng(heads + rows), cu[-1], d, 3.0, "bf16")
     x = qkv.astype(np.float64)
