@@ -77,8 +77,10 @@ template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl<0, N>(f); }
 
 // Workgroup `block` of a launch's touching workgroups (a multiple of 8, of nt threads each) reads a word of every line that is
-// its own.  Workgroup ids modulo 8 are XCDs: each takes one contiguous eighth of a matrix, the rows that the product's
-// workgroups on that XCD read (they walk the columns of the output in such eighths).
+// its own.  Workgroup ids modulo 8 are XCDs: each takes one contiguous eighth of the bytes that are touched.  Those are the rows
+// that the product's workgroups on that XCD read where the whole matrix is touched and the output has at most eight tiles of
+// rows (the workgroups then walk its columns in such eighths).  Elsewhere, for a matrix that touch_blocks cut short or an
+// output of more rows, other XCDs read most of the lines, and what is gained is that they come from the last-level cache.
 __device__ __forceinline__ void touch_lines(const Touch& t, unsigned block, unsigned blocks, unsigned nt) {
   const uint32_t part = block & 7, stride = (blocks >> 3) * nt;
   for (int r = 0; r < 4; ++r) {
