@@ -248,7 +248,7 @@ __device__ __forceinline__ void attention(const AttnArgs& a) {
   // so a score leaves the MFMA as the exponent itself and no subtraction per element follows.  The matrix unit wants its
   // start values in a register each: 16 that hold the same number and are rewritten only when the reference moves (32 for
   // two query tiles would not fit).  63 -> 45 vector instructions for 32 keys: 28 x 577 tokens, 16 heads of 64, 69.0 -> 63.4 us;
-  // 5 x 729, heads of 80, 26.5 -> 24.4; 1120 tokens 19.9 -> 18.6.
+  // 5 x 729, heads of 80, 26.5 -> 24.4.
   // `limit`: the largest exponent that does not move the reference (-inf until a block has set it).
   constexpr bool NEGM = PRESC && !FAST && NT == 1;
   f32x16 negm;
